@@ -113,11 +113,14 @@ typedef struct idb_controller_state {
  *               selection used (debug / parity; the arithmetic is unchanged).
  *   workspace   device scratch of at least idb_router_workspace_bytes().
  *   variant     0 = automatic tiling; other values force a tiling (see
- *               idb_router_variant_info).  Variants 1-5 (32x32 MFMA tiles)
- *               give identical outputs; variant 6 (16x16 tiles) accumulates
- *               the contraction in another order, so its scores can differ
- *               in the last fp32 bits.  Given its scores, every variant's
- *               selection, gate weights and counts are exact.
+ *               idb_router_variant_info).  Variants 1-5, 8 and 9 (32x32 MFMA
+ *               tiles) give identical outputs; variants 6, 7 and 10 (16x16
+ *               tiles) accumulate the contraction in another order, so their
+ *               scores can differ in the last fp32 bits.  Given its scores,
+ *               every variant's selection, gate weights and counts are exact.
+ *               The automatic choice depends on T only among tilings of the
+ *               same accumulation order: a token's outputs do not depend on
+ *               the batch it comes in.
  * The T x E score matrix is never written to memory unless scores_dump is set.
  * ------------------------------------------------------------------------- */
 size_t idb_router_workspace_bytes(int64_t T, int32_t d, int32_t E, int32_t K, idb_dtype dtype, int32_t variant);

@@ -35,11 +35,11 @@ constexpr int kMaxKGpu = 32;
 
 size_t round_up(size_t n) { return (n + 255) & ~size_t(255); }
 
-// Resolve a router variant for a shape; returns IDB_OK and the tiling, or an error.
+// Resolve a router variant for a shape (T tokens of E experts); returns IDB_OK and the tiling, or an error.
 // one_slice: only tilings whose workgroups cover all E experts and that have
 // the softmax mode (the auxiliary-loss statistics need each token's whole
 // softmax in one workgroup).
-idb_status resolve_tiling(int32_t E, idb_dtype dtype, int32_t variant, idb::RouterTiling* out,
+idb_status resolve_tiling(int64_t T, int32_t E, idb_dtype dtype, int32_t variant, idb::RouterTiling* out,
                           bool one_slice = false) {
     const int n = idb::router_tiling_count();
     const int want_f32 = dtype == IDB_DTYPE_F32;
@@ -76,7 +76,7 @@ idb_status resolve_tiling(int32_t E, idb_dtype dtype, int32_t variant, idb::Rout
     if (!found)
         return fail(IDB_ERR_UNSUPPORTED, one_slice ? "no one-slice router tiling for E=%d" : "no router tiling for E=%d",
                     E);
-    *out = best;
+    *out = idb::router_tiling_for(best, T, E);
     return IDB_OK;
 }
 
@@ -140,7 +140,7 @@ idb_status prepare_router(const void* x, const void* W_g, idb_dtype dtype, idb_w
     if (!expert_idx || !gate_w || !counts) return fail(IDB_ERR_INVALID_ARG, "null output pointer");
     if (!aligned(expert_idx, 4) || !aligned(gate_w, 4) || !aligned(counts, 4))
         return fail(IDB_ERR_INVALID_ARG, "outputs must be 4-byte aligned");
-    st = resolve_tiling(E, dtype, variant, &call->tiling, aux);
+    st = resolve_tiling(T, E, dtype, variant, &call->tiling, aux);
     if (st != IDB_OK) return st;
     const size_t need = aux ? aux_ws_bytes(T, E, call->tiling) : router_ws_bytes(T, E, KL, call->tiling);
     if (need > 0) {
@@ -212,7 +212,7 @@ extern "C" {
 size_t idb_router_workspace_bytes(int64_t T, int32_t d, int32_t E, int32_t K, idb_dtype dtype, int32_t variant) {
     if (check_router_shape(T, d, E, K, dtype) != IDB_OK) return 0;
     idb::RouterTiling t;
-    if (resolve_tiling(E, dtype, variant, &t) != IDB_OK) return 0;
+    if (resolve_tiling(T, E, dtype, variant, &t) != IDB_OK) return 0;
     return router_ws_bytes(T, E, K, t);
 }
 
@@ -222,7 +222,7 @@ idb_status idb_router_variant_info(int64_t T, int32_t d, int32_t E, int32_t K, i
     idb_status st = check_router_shape(T, d, E, K, dtype);
     if (st != IDB_OK) return st;
     idb::RouterTiling t;
-    st = resolve_tiling(E, dtype, variant, &t);
+    st = resolve_tiling(T, E, dtype, variant, &t);
     if (st != IDB_OK) return st;
     out[0] = t.bt;
     out[1] = idb::router_slices(t, E);
@@ -425,7 +425,7 @@ idb_status idb_router_step_noalloc(const void* x, const void* W_g, idb_dtype dty
     st = check_router_shape(T, d, cfg->E, K, dtype);
     if (st != IDB_OK) return st;
     idb::RouterTiling t;
-    st = resolve_tiling(cfg->E, dtype, variant, &t);
+    st = resolve_tiling(T, cfg->E, dtype, variant, &t);
     if (st != IDB_OK) return st;
     const size_t need = router_ws_bytes(T, cfg->E, K, t);
     const size_t have = idb::noalloc_scratch_bytes();
@@ -467,7 +467,7 @@ size_t idb_qb_router_workspace_bytes(int64_t T, int32_t d, int32_t E, int32_t K,
                                      int32_t variant) {
     if (K < 1 || check_router_shape(T, d, E, K + 1, dtype) != IDB_OK) return 0;
     idb::RouterTiling t;
-    if (resolve_tiling(E, dtype, variant, &t) != IDB_OK) return 0;
+    if (resolve_tiling(T, E, dtype, variant, &t) != IDB_OK) return 0;
     return router_ws_bytes(T, E, K + 1, t);
 }
 
@@ -511,7 +511,7 @@ size_t idb_aux_router_workspace_bytes(int64_t T, int32_t d, int32_t E, int32_t K
                                       int32_t variant) {
     if (check_router_shape(T, d, E, K, dtype) != IDB_OK) return 0;
     idb::RouterTiling t;
-    if (resolve_tiling(E, dtype, variant, &t, true) != IDB_OK) return 0;
+    if (resolve_tiling(T, E, dtype, variant, &t, true) != IDB_OK) return 0;
     return aux_ws_bytes(T, E, t);
 }
 

@@ -119,6 +119,35 @@ __device__ __forceinline__ uint4 bload16(__amdgpu_buffer_rsrc_t r, int voff, int
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 u) { return __builtin_bit_cast(bf16x8, u); }
 
+// One 16-byte unit of both operands: bf16 -> one 32x32x16 MFMA; fp32 -> four
+// 32x32x2 MFMAs, float i of each lane's unit feeding the i-th.
+template <bool F32>
+__device__ __forceinline__ floatx16 mfma_unit(uint4 a, uint4 b, floatx16 c) {
+    if constexpr (F32) {
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, a.x), __builtin_bit_cast(float, b.x), c,
+                                                 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, a.y), __builtin_bit_cast(float, b.y), c,
+                                                 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, a.z), __builtin_bit_cast(float, b.z), c,
+                                                 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, a.w), __builtin_bit_cast(float, b.w), c,
+                                                 0, 0, 0);
+        return c;
+    } else {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(b), c, 0, 0, 0);
+    }
+}
+
+// XCD-aware block order: consecutive blocks land on different XCDs, so remap
+// to give each XCD a contiguous run of (tile, slice) pairs; the slices of one
+// token tile then share their token rows in that XCD's L2.
+__device__ __forceinline__ int xcd_block_order() {
+    const int nb = gridDim.x;
+    int L = blockIdx.x;
+    if ((nb & 7) == 0) L = (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3);
+    return L;
+}
+
 // Gate weights of one token from its selected unbiased scores in rank order:
 // den is the fp32 sum in rank order; w_r = s_r / den (IEEE division); den == 0
 // gives 1/K.

@@ -67,6 +67,9 @@ struct RouterTiling {
 // Number of known tilings and the i-th one (0-based).
 int router_tiling_count();
 RouterTiling router_tiling(int i);
+// The tiling an automatic choice of t runs T tokens on: t, or its half-size
+// twin for small batches (the same slices, workspace and scores).
+RouterTiling router_tiling_for(const RouterTiling& t, int64_t T, int E);
 
 struct RouterArgs {
     const void* x;

@@ -53,35 +53,6 @@ namespace {
 constexpr int kRowPad = 160;  // LDS bytes per staged token row (128 + 32 pad)
 constexpr int kMaxSlices = 8;
 
-// One 16-byte unit of both operands: bf16 -> one 32x32x16 MFMA; fp32 -> four
-// 32x32x2 MFMAs, float i of each lane's unit feeding the i-th.
-template <bool F32>
-__device__ __forceinline__ floatx16 mfma_unit(uint4 a, uint4 b, floatx16 c) {
-    if constexpr (F32) {
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, a.x), __builtin_bit_cast(float, b.x), c,
-                                                 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, a.y), __builtin_bit_cast(float, b.y), c,
-                                                 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, a.z), __builtin_bit_cast(float, b.z), c,
-                                                 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, a.w), __builtin_bit_cast(float, b.w), c,
-                                                 0, 0, 0);
-        return c;
-    } else {
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(b), c, 0, 0, 0);
-    }
-}
-
-// XCD-aware block order: consecutive blocks land on different XCDs, so remap
-// to give each XCD a contiguous run of (tile, slice) pairs; the slices of one
-// token tile then share their token rows in that XCD's L2.
-__device__ __forceinline__ int xcd_block_order() {
-    const int nb = gridDim.x;
-    int L = blockIdx.x;
-    if ((nb & 7) == 0) L = (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3);
-    return L;
-}
-
 template <bool F32, int WAVES, int TBW, int NBLK>
 struct Cfg32 {
     static constexpr int NT = WAVES * 64;
@@ -479,6 +450,21 @@ __global__ __launch_bounds__(WAVES * 64) void router16_kernel(RouterArgs a, int 
     select_epilogue<EC, SM>(a, NS, slice, tok0, smem, breg, store_pass);
 }
 
+// How many of a slice's n rank-ordered (descending) keys are above k, by
+// binary search: the lists come sorted out of the epilogue.  Against a scan of
+// the list, whole steps at K = 16, T = 4096, d = 2048 (64 candidates per token
+// at E = 1024): 95.6 -> 88.5 us together with 8-wave tiles.
+__device__ __forceinline__ int count_above(const unsigned long long* list, int n, unsigned long long k) {
+    int lo = 0;
+    while (n > 0) {
+        const int half = n >> 1;
+        const bool above = list[lo + half] > k;
+        lo = above ? lo + half + 1 : lo;
+        n = above ? n - half - 1 : half;
+    }
+    return lo;
+}
+
 // Merge the slices' rank-ordered candidate lists into the final Top-K, compute
 // the gate weights and count the assignments.  One thread per candidate: its
 // final rank is its position in its own slice's list plus the number of the
@@ -519,11 +505,8 @@ __global__ __launch_bounds__(kMergeThreads) void router_merge_kernel(RouterArgs 
         __syncthreads();
         int rank = r;
         if (act) {
-            for (int o = 0; o < NS; ++o) {
-                if (o == sl) continue;
-                const int b = tt * per_tok + o * KL;
-                for (int j = 0; j < KL; ++j) rank += (key[b + j] > k) ? 1 : 0;
-            }
+            for (int o = 0; o < NS; ++o)
+                if (o != sl) rank += count_above(key + tt * per_tok + o * KL, KL, k);
             if (rank < K) {
                 sel[tt * K + rank] = s;
                 a.idx[tok * K + rank] = e;
@@ -650,12 +633,8 @@ __global__ __launch_bounds__(kTileThreads) void router_merge_tile_kernel(RouterA
                 const int sl = pos / KL, r = pos - sl * KL;
                 const unsigned long long k = mk[c];
                 int rank = r;
-                for (int o = 0; o < NS; ++o) {
-                    if (o == sl) continue;
-                    const unsigned long long* lo = mk + t * NSK + o * KL;
-#pragma unroll 8
-                    for (int j = 0; j < KL; ++j) rank += (lo[j] > k) ? 1 : 0;
-                }
+                for (int o = 0; o < NS; ++o)
+                    if (o != sl) rank += count_above(mk + t * NSK + o * KL, KL, k);
                 if (rank < K) {
                     msel[t * kMaxK + rank] = ms[c];
                     midx[t * kMaxK + rank] = (int)~(unsigned)k;
@@ -757,6 +736,9 @@ hipError_t launch_layout(const RouterTiling& t, const RouterArgs& a, int NS, hip
         case 5: return launch32<true, PACKED, 4, 4, 1>(a, NS, stream, e0, e1);
         case 6: return launch16<PACKED, 8, 8, 3>(a, NS, stream, e0, e1);
         case 7: return launch16<PACKED, 8, 4, 6>(a, NS, stream, e0, e1);
+        case 8: return launch32<false, PACKED, 8, 4, 1>(a, NS, stream, e0, e1);
+        case 9: return launch32<false, PACKED, 8, 2, 1>(a, NS, stream, e0, e1);
+        case 10: return launch16<PACKED, 8, 4, 3>(a, NS, stream, e0, e1);
         default: return hipErrorInvalidValue;
     }
 }
@@ -767,17 +749,41 @@ hipError_t launch_layout(const RouterTiling& t, const RouterArgs& a, int NS, hip
 const RouterTiling kTilings[] = {
     {1, 0, 4, 128, 96, 2, 0},  // bf16 32x32 tiles: 128 tokens x 384 experts per workgroup
     {2, 0, 8, 64, 96, 5, 1},   // bf16 32x32 tiles: 64 tokens x 768 experts
-    {3, 0, 4, 128, 64, 3, 0},  // bf16 32x32 tiles: 128 tokens x 256 experts
+    {3, 0, 4, 128, 64, 9, 0},  // bf16 32x32 tiles: 128 tokens x 256 experts
     {4, 0, 4, 128, 32, 4, 1},  // bf16 32x32 tiles: 128 tokens x 128 experts
     {5, 1, 4, 128, 32, 0, 1},  // fp32 32x32 tiles: 128 tokens x 128 experts
     {6, 0, 8, 128, 48, 0, 0},  // bf16 16x16 tiles: 128 tokens x 384 experts, two waves per SIMD
     {7, 0, 8, 64, 96, 1, 1},   // bf16 16x16 tiles: 64 tokens x 768 experts, two waves per SIMD
+    // as tiling 3 with two waves per SIMD, which hide each other's chunk barrier
+    // and operand reads; whole step at d = 2048, K = 8, E = 256: T = 32768
+    // 63.1 -> 53.1 us, T = 50001 123.1 -> 102.9 us
+    {8, 0, 8, 128, 32, 3, 0},  // bf16 32x32 tiles: 128 tokens x 256 experts
+    {9, 0, 8, 64, 32, 9, 0},   // bf16 32x32 tiles: 64 tokens x 256 experts, two waves per SIMD
+    {10, 0, 8, 64, 48, 9, 0},  // bf16 16x16 tiles: 64 tokens x 384 experts, two waves per SIMD
 };
+
+// The half-size twin (64 instead of 128 tokens per workgroup, the same expert
+// slices and accumulation order) of a tiling, 0 if none.
+int half_tile(int id) { return id == 6 ? 10 : id == 8 ? 9 : 0; }
 
 }  // namespace
 
 int router_tiling_count() { return (int)(sizeof(kTilings) / sizeof(kTilings[0])); }
 RouterTiling router_tiling(int i) { return kTilings[i]; }
+
+// A launch takes as many rounds as its workgroups need over the CUs, and a
+// round costs about the same whatever share of the CUs it fills.  So a batch
+// whose 64-token tiles still fit one round takes those: measured per whole
+// step at d = 2048, K = 8, 128- against 64-token tiles, us: E = 768, T = 4096:
+// 49.4 -> 37.4, T = 8192 (256 tiles): 50.1 -> 40.9, T = 12288: 54.2 -> 65.7;
+// E = 256, T = 16384 (256 tiles): 45.6 -> 37.2, T = 32768: 53.1 -> 66.5;
+// E = 1024, T = 4096: 57.8 -> 46.0, T = 6144: 58.4 -> 65.4.
+RouterTiling router_tiling_for(const RouterTiling& t, int64_t T, int E) {
+    constexpr int64_t kCus = 256;  // MI355X; a constant, so that a shape's tiling needs no HIP call
+    const int half = half_tile(t.id);
+    if (half && (T + 63) / 64 * router_slices(t, E) <= kCus) return kTilings[half - 1];
+    return t;
+}
 
 hipError_t launch_router_score_select(const RouterTiling& t, const RouterArgs& a, hipStream_t stream,
                                       hipEvent_t start, hipEvent_t stop) {
