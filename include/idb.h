@@ -121,7 +121,11 @@ typedef struct idb_controller_state {
  *               The automatic choice depends on T only among tilings of the
  *               same accumulation order: a token's outputs do not depend on
  *               the batch it comes in.
- * The T x E score matrix is never written to memory unless scores_dump is set.
+ * With variant 0 a small batch, or one with a large K, may go through a T x E
+ * score matrix in the workspace (at most 256 MB, counted in
+ * idb_router_workspace_bytes) when the workspace has room for it; with less
+ * room, or with a forced variant, the score matrix is never written to memory
+ * unless scores_dump is set.  The outputs are the same bits either way.
  * ------------------------------------------------------------------------- */
 size_t idb_router_workspace_bytes(int64_t T, int32_t d, int32_t E, int32_t K, idb_dtype dtype, int32_t variant);
 

@@ -102,6 +102,50 @@ size_t router_ws_bytes(int64_t T, int32_t E, int32_t K, const idb::RouterTiling&
     return 3 * round_up((size_t)T * ns * K * 4) + 256;
 }
 
+// Scored path: whether the automatic choice routes this shape through
+// materialised scores (scores.hip, then the selection of select.hip) instead
+// of the fused tiling t.  It has small tiles for small batches and a selection
+// that keeps its speed for large K, but writes and reads T x E scores, so the
+// fused kernel takes over as the batch grows.  The lines below are where whole
+// steps cross (scored against fused, us, d = 2048 unless said):
+//  - fp32: E = 256 T = 8192 45.5 / 53.9, T = 12288 60.5 / 54.5; E = 64 T = 32768
+//    46.5 / 55.0 (d = 512)
+//  - 128-expert tiles: E = 128 T = 16384 32.4 / 38.9, T = 32768 61.7 / 43.9
+//  - K = 8 on 64-token tiles: E = 768 T = 2048 28.6 / 37.3, T = 4096 37.2 / 37.4;
+//    E = 256 T = 3072 24.6 / 28.5, T = 4096 28.8 / 28.8; with d = 512 E = 768 T = 2048
+//    22.3 / 21.2
+//  - K > 12 (the fused lists overflow, the slice merge grows): K = 16 E = 768
+//    T = 50001 245 / 359; E = 512 T = 16384 70.4 / 71.4; E = 1024 T = 16384 142 / 139
+//  - a row-major router matrix, which the fused kernels read at a quarter to
+//    half of the packed rate and the scored path packs first: E = 256 T = 16384
+//    45.6 / 51.1, T = 32768 91.7 / 59.7; E = 768 T = 8192 51.9 / 70.9; E = 1024 T = 8192
+//    66.5 / 64.7
+bool use_scores(int64_t T, int32_t E, int32_t K, const idb::RouterTiling& t, bool row_major) {
+    const int64_t n = T * E;
+    if (n > (int64_t(64) << 20)) return false;  // 256 MB of scores
+    if (t.is_f32) return n <= (int64_t(2) << 20);
+    if (t.id == 4) return E <= 128 ? T <= 20480 : n <= (int64_t(6) << 20);
+    if (K > 12) {
+        if (K > 20 || idb::tiling_is_16(t)) return true;
+        return n <= (int64_t(idb::router_slices(t, E) > 1 ? 12 : 3) << 20);
+    }
+    if (row_major && n <= (int64_t(6) << 20)) return true;
+    return T <= 2560;
+}
+
+// From this many tokens on the scored path packs a row-major router matrix
+// into its workspace first (about 4 us; T = 777 E = 256: 12.9 us unpacked, 11.9
+// packed; T = 1024 E = 1024: 40 us unpacked, 29 packed).  Not fp32, whose MFMAs
+// take long enough to cover the loads (T = 4096, d = 256, E = 64: 7.4 us
+// unpacked, 8.4 packed).
+constexpr int64_t kPackTokens = 1024;
+
+size_t weight_bytes(int32_t E, int32_t d) { return (size_t)E * d * 2; }
+
+// Its workspace: the scores [T][E], the ticket, then (when there is room) the
+// packed router matrix.
+size_t score_ws_bytes(int64_t T, int32_t E) { return round_up((size_t)T * E * 4) + 256; }
+
 // Auxiliary-loss statistics: per-tile softmax column sums [tiles][E] fp32,
 // per-tile counts [tiles][E] int32, kAuxMaxBlocks block records, the ticket.
 size_t aux_rows_bytes(int64_t T, int32_t E, const idb::RouterTiling& t) {
@@ -116,6 +160,8 @@ struct RouterCall {
     idb::RouterArgs args;
     unsigned* ticket;  // the merge's (multi-slice tilings) or the statistics kernel's ticket
     idb::AuxPartial* aux_partial;  // auxiliary-loss statistics: block records
+    bool scored;                   // the scored path: launch_scores, then launch_select_step
+    char* pack_to;                 // scored: nullable, where a row-major router matrix is packed first
 };
 
 idb_status prepare_router(const void* x, const void* W_g, idb_dtype dtype, idb_weight_layout layout,
@@ -123,7 +169,10 @@ idb_status prepare_router(const void* x, const void* W_g, idb_dtype dtype, idb_w
                           int32_t E, int32_t K, int32_t* expert_idx, float* gate_w, int32_t* counts,
                           int32_t accumulate_counts, float* scores_dump, void* workspace, size_t workspace_bytes,
                           int32_t variant, bool need_inputs, RouterCall* call, bool qb = false,
-                          bool aux = false) {
+                          bool aux = false, bool whole = false) {
+    // whole: the call makes all of the step's launches itself (the split calls
+    // keep the fused tiling, whose slices their callers can query), so the
+    // automatic choice may take the scored path
     // Quantile Balancing keeps K + 1 candidates per token (the (K+1)-th is the cutoff)
     const int32_t KL = qb ? K + 1 : K;
     idb_status st = check_router_shape(T, d, E, KL, dtype);
@@ -173,11 +222,29 @@ idb_status prepare_router(const void* x, const void* W_g, idb_dtype dtype, idb_w
     a.ticket = need ? reinterpret_cast<unsigned*>(ws + 3 * part) : nullptr;
     a.alpha = nullptr;
     a.scores_t = nullptr;
+    a.scores = nullptr;
     a.softmax = aux ? 1 : 0;
     a.prob_part = nullptr;
     a.cnt_part = nullptr;
     call->ticket = need ? reinterpret_cast<unsigned*>(ws + 3 * part) : nullptr;
     call->aux_partial = nullptr;
+    // The scored path may need more scratch than the fused tiling: a workspace
+    // that was sized for another batch keeps the fused one.
+    const size_t scored_need = score_ws_bytes(T, E);
+    call->scored = whole && variant == 0 && workspace && workspace_bytes >= scored_need && aligned(workspace, 16) &&
+                   use_scores(T, E, K, call->tiling, layout == IDB_WEIGHT_ROW_MAJOR);
+    call->pack_to = nullptr;
+    if (call->scored) {
+        a.scores = reinterpret_cast<float*>(ws);
+        call->ticket = reinterpret_cast<unsigned*>(ws + scored_need - 256);
+        a.ticket = call->ticket;
+        a.zero_counts = accumulate_counts ? 0 : 1;
+        a.cand_v = a.cand_s = nullptr;
+        a.cand_i = nullptr;
+        if (layout == IDB_WEIGHT_ROW_MAJOR && T >= kPackTokens && dtype == IDB_DTYPE_BF16 &&
+            workspace_bytes - scored_need >= weight_bytes(E, d))
+            call->pack_to = ws + scored_need;
+    }
     if (aux) {
         // one slice: no candidates; the statistics' per-tile rows instead
         const size_t rows = aux_rows_bytes(T, E, call->tiling);
@@ -196,6 +263,17 @@ idb_status prepare_router(const void* x, const void* W_g, idb_dtype dtype, idb_w
 
 idb_status enqueue_score_select(const RouterCall& c, int32_t accumulate_counts, hipStream_t stream,
                                 hipEvent_t start = nullptr, hipEvent_t stop = nullptr) {
+    if (c.scored) {
+        idb::RouterArgs a = c.args;
+        if (c.pack_to) {
+            idb_status st = hip_result(idb::launch_pack_weight(a.W, c.pack_to, a.E, (int64_t)a.d * 2, stream),
+                                       "pack weight launch");
+            if (st != IDB_OK) return st;
+            a.W = c.pack_to;
+            a.w_packed = 1;
+        }
+        return hip_result(idb::launch_scores(c.tiling, a, stream), "router score launch");
+    }
     const int ns = idb::router_slices(c.tiling, c.args.E);
     if (ns <= 1 && !accumulate_counts && !c.args.cnt_part) {
         idb_status st = hip_result(idb::launch_fill_i32(c.args.counts, 0, c.args.E, stream), "zero counts");
@@ -213,7 +291,11 @@ size_t idb_router_workspace_bytes(int64_t T, int32_t d, int32_t E, int32_t K, id
     if (check_router_shape(T, d, E, K, dtype) != IDB_OK) return 0;
     idb::RouterTiling t;
     if (resolve_tiling(T, E, dtype, variant, &t) != IDB_OK) return 0;
-    return router_ws_bytes(T, E, K, t);
+    const size_t fused = router_ws_bytes(T, E, K, t);
+    // room for the path either weight layout may take
+    if (variant != 0 || !(use_scores(T, E, K, t, false) || use_scores(T, E, K, t, true))) return fused;
+    const size_t scored = score_ws_bytes(T, E) + (T >= kPackTokens ? weight_bytes(E, d) : 0);
+    return scored > fused ? scored : fused;
 }
 
 idb_status idb_router_variant_info(int64_t T, int32_t d, int32_t E, int32_t K, idb_dtype dtype, int32_t variant,
@@ -272,10 +354,11 @@ idb_status idb_router_forward(const void* x, const void* W_g, idb_dtype dtype, i
                               void* workspace, size_t workspace_bytes, int32_t variant, hipStream_t stream) {
     RouterCall c;
     idb_status st = prepare_router(x, W_g, dtype, weight_layout, bias, T, d, E, K, expert_idx, gate_w, counts, accumulate_counts,
-                                   scores_dump, workspace, workspace_bytes, variant, true, &c);
+                                   scores_dump, workspace, workspace_bytes, variant, true, &c, false, false, true);
     if (st != IDB_OK) return st;
     st = enqueue_score_select(c, accumulate_counts, stream);
     if (st != IDB_OK) return st;
+    if (c.scored) return hip_result(idb::launch_select_step(c.args, c.args.scores, nullptr, stream), "select launch");
     return hip_result(idb::launch_router_merge(c.tiling, c.args, nullptr, stream), "router merge launch");
 }
 
@@ -368,6 +451,7 @@ idb_status enqueue_merge_step(const RouterCall& c, const idb_controller_cfg* cfg
     k.status = state->status;
     k.stats = out_maxvio_minvio;
     k.ticket = c.ticket;
+    if (c.scored) return hip_result(idb::launch_select_step(c.args, c.args.scores, &k, stream), "select launch");
     return hip_result(idb::launch_router_merge(c.tiling, c.args, &k, stream), "router merge launch");
 }
 
@@ -394,7 +478,7 @@ idb_status idb_router_step(const void* x, const void* W_g, idb_dtype dtype, idb_
     if (st != IDB_OK) return st;
     RouterCall c;
     st = prepare_router(x, W_g, dtype, weight_layout, state->bias, T, d, cfg->E, K, expert_idx, gate_w, counts,
-                        accumulate_counts, nullptr, workspace, workspace_bytes, variant, true, &c);
+                        accumulate_counts, nullptr, workspace, workspace_bytes, variant, true, &c, false, false, true);
     if (st != IDB_OK) return st;
     st = enqueue_score_select(c, accumulate_counts, stream);
     if (st != IDB_OK) return st;
@@ -445,7 +529,10 @@ idb_status idb_router_step_noalloc(const void* x, const void* W_g, idb_dtype dty
         if (st != IDB_OK) return st;
     }
     void* ws = nullptr;
-    if (need > 0) {
+    // one-slice tilings need no scratch; the scored path uses it when it fits
+    const bool scratch = need > 0 || (variant == 0 && score_ws_bytes(T, cfg->E) <= have &&
+                                      use_scores(T, cfg->E, K, t, weight_layout == IDB_WEIGHT_ROW_MAJOR));
+    if (scratch) {
         int dev = -1;
         st = hip_result(hipGetDevice(&dev), "current device");
         if (st != IDB_OK) return st;
@@ -460,7 +547,7 @@ idb_status idb_router_step_noalloc(const void* x, const void* W_g, idb_dtype dty
         if (st != IDB_OK) return st;
     }
     return idb_router_step(x, W_g, dtype, weight_layout, T, d, K, cfg, state, expert_idx, gate_w, counts,
-                           accumulate_counts, out_maxvio_minvio, ws, need > 0 ? have : 0, variant, stream);
+                           accumulate_counts, out_maxvio_minvio, ws, scratch ? have : 0, variant, stream);
 }
 
 size_t idb_qb_router_workspace_bytes(int64_t T, int32_t d, int32_t E, int32_t K, idb_dtype dtype,

@@ -71,6 +71,9 @@ RouterTiling router_tiling(int i);
 // twin for small batches (the same slices, workspace and scores).
 RouterTiling router_tiling_for(const RouterTiling& t, int64_t T, int E);
 
+// 16x16x32 MFMA accumulation order (else 32x32x16, fp32 32x32x2).
+inline bool tiling_is_16(const RouterTiling& t) { return t.id == 6 || t.id == 7 || t.id == 10; }
+
 struct RouterArgs {
     const void* x;
     const void* W;
@@ -86,6 +89,7 @@ struct RouterArgs {
     int zero_counts;  // workgroup 0 of the multi-slice kernel zeroes counts
     unsigned* ticket;  // nullable; workgroup 0 of the multi-slice kernel zeroes it
     float* dump;
+    float* scores;  // scored path: the [T][E] scores in the workspace, 16-byte aligned
     // multi-slice candidates in the workspace: [T][slices][KL], KL = K, or
     // K + 1 with alpha set
     float* cand_v;
@@ -126,6 +130,11 @@ struct CtrlArgs {
     unsigned* ticket;
 };
 
+// Selection from the scores [T][E] (E % 4 == 0, 16-byte aligned) for a.T, a.E,
+// a.K, a.bias into a.idx, a.w, a.counts (which hold the starting values); with
+// ctrl, the last workgroup applies the controller update.
+hipError_t launch_select_step(const RouterArgs& a, const float* scores, const CtrlArgs* ctrl, hipStream_t stream);
+
 // start/stop: nullable events that take the kernel's own start and end
 // timestamps (an extended launch; measurement only).
 hipError_t launch_router_score_select(const RouterTiling& t, const RouterArgs& a, hipStream_t stream,
@@ -134,6 +143,10 @@ hipError_t launch_router_score_select(const RouterTiling& t, const RouterArgs& a
 // finished counts (multi-slice tilings only).
 hipError_t launch_router_merge(const RouterTiling& t, const RouterArgs& a, const CtrlArgs* ctrl,
                                hipStream_t stream);
+// Scored path (scores.hip): s = sigmoid(W x) of every token into a.scores (and
+// a.dump), in the accumulation order of tiling t; zeroes counts (a.zero_counts)
+// and the ticket.
+hipError_t launch_scores(const RouterTiling& t, const RouterArgs& a, hipStream_t stream);
 // Router matrix [E][d] (row_bytes per row) -> the packed A-operand layout.
 hipError_t launch_pack_weight(const void* W, void* P, int E, int64_t row_bytes, hipStream_t stream);
 

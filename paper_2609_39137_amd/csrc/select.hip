@@ -4,13 +4,18 @@
 // pass over a materialised T x E score matrix.
 //
 // Two kernels:
-//  * select_reg_kernel (K <= 10, E % 4 == 0, 16-byte aligned scores): 16 lanes
-//    (one DPP row) per token, each holding every 16th float4 of the row in
-//    registers.  The K-th largest of the 16 lane maxima is a lower bound tau of
-//    the token's K-th largest biased score; only the float4 chunks whose
-//    maximum reaches tau are read again, and their values >= tau go to a short
-//    LDS list whose entries are ranked by counting.  A token whose list would
-//    overflow takes K exact argmax rounds over its row instead.
+//  * select_reg_kernel (E % 4 == 0, 16-byte aligned scores): 16 lanes (one DPP
+//    row) per token, each holding every 16th float4 of the row in registers.
+//    The K-th largest of the row's 16 G group maxima (G = 1, 2 or 4 groups per
+//    lane) is a lower bound tau of the token's K-th largest biased score; only
+//    the float4 chunks whose maximum reaches tau are read again, and their
+//    values >= tau go to a short LDS list whose entries are ranked by counting.
+//    A token whose list would overflow takes K exact argmax rounds over its row
+//    instead.  G grows with K so that the list stays short: K of 16 G groups
+//    holding K or more values gives about 16 G ln(1 / (1 - K / 16 G)) of them
+//    (16 at K = 10, G = 1; 22 at K = 16, G = 2; 44 at K = 32, G = 4), and with
+//    G = 1 every list overflows from K = 16 on.  It also ends the router's
+//    scored path, where its last workgroup applies the controller update.
 //  * select_kernel (every other case): a workgroup of 512 threads walks tiles
 //    of 32 tokens (grid-stride, one workgroup per CU: the score rows of a tile
 //    take most of the LDS).  A tile's scores go from registers into the LDS
@@ -20,6 +25,7 @@
 //    current tile.
 // Both flush their LDS histogram once per workgroup.
 #include "common.h"
+#include "controller_block.h"
 #include "epilogue.h"
 #include "internal.h"
 
@@ -122,7 +128,6 @@ hipError_t launch_select_be(const RouterArgs& a, const float* scores, hipStream_
 
 // ---------------------------------------------------------------------------
 // Register-resident selection.
-constexpr int kRegMaxK = 10;   // largest K of this kernel
 constexpr int kRegCap = 64;    // candidate list entries per token
 constexpr int kRegStage = 4;   // marked chunks per lane staged in LDS
 
@@ -136,10 +141,21 @@ __device__ __forceinline__ float row_rorf(float x) {
     return __uint_as_float(row_ror<R>(__float_as_uint(x)));
 }
 
-// Number of lanes of the row whose value is strictly greater than this lane's.
-template <int... R>
-__device__ __forceinline__ int row_count_greater(float m, std::integer_sequence<int, R...>) {
-    return ((row_rorf<R + 1>(m) > m ? 1 : 0) + ...);
+// For each of this lane's G values: how many of the row's 16 G values are
+// strictly greater.
+template <int R, int G>
+__device__ __forceinline__ void count_greater_step(const float (&m)[G], int (&gt)[G]) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const float o = R == 0 ? m[g] : row_rorf<R == 0 ? 1 : R>(m[g]);
+#pragma unroll
+        for (int i = 0; i < G; ++i) gt[i] += o > m[i] ? 1 : 0;
+    }
+}
+template <int G, int... R>
+__device__ __forceinline__ void row_count_greater(const float (&m)[G], int (&gt)[G],
+                                                  std::integer_sequence<int, R...>) {
+    (count_greater_step<R, G>(m, gt), ...);
 }
 
 __device__ __forceinline__ float row_min(float x) {
@@ -180,7 +196,6 @@ template <int NV>
 __device__ __forceinline__ void overflow_select(const float* row, const float* bias_s, unsigned vmask, int j, int K,
                                                 int* sel_i, float* sel_s) {
     unsigned long long prev = ~0ull;
-    int mine = 0;
     for (int r = 0; r < K; ++r) {
         unsigned long long best = 0ull;
 #pragma unroll 1
@@ -199,27 +214,31 @@ __device__ __forceinline__ void overflow_select(const float* row, const float* b
         }
         best = row_max_key(best);
         prev = best;
-        if (j == r) mine = (int)~(unsigned)best;
-    }
-    if (j < K) {
-        sel_i[j] = mine;
-        sel_s[j] = row[mine];
+        if (j == (r & 15)) {
+            const int e = (int)~(unsigned)best;
+            sel_i[r] = e;
+            sel_s[r] = row[e];
+        }
     }
 }
 
 // NV: float4 chunks per lane (64 NV >= E).  Lane j of a token's row owns the
-// columns 4 (16 c + j) .. +3 for c < NV.
-template <int NV, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void select_reg_kernel(RouterArgs a, const float* __restrict__ scores) {
+// columns 4 (16 c + j) .. +3 for c < NV.  G: group maxima per lane (1, 2 or 4).
+// TAIL: the last workgroup applies the controller update.
+template <int NV, int WAVES, int G, bool TAIL>
+__global__ __launch_bounds__(64 * WAVES) void select_reg_kernel(RouterArgs a, const float* __restrict__ scores,
+                                                                CtrlArgs ctrl) {
     constexpr int BE = 64 * NV;
     constexpr int TPB = 4 * WAVES;  // tokens per workgroup tile (4 per wave)
+    constexpr int kMaxSel = G == 4 ? kMaxK : 16;  // largest K
     __shared__ __attribute__((aligned(16))) float bias_s[BE];
     __shared__ int hist[BE];
     __shared__ int cnt[TPB];
     __shared__ unsigned long long lkey[TPB][kRegCap];
     __shared__ float lsc[TPB][kRegCap];
-    __shared__ int sel_i[TPB][kRegMaxK];
-    __shared__ float sel_s[TPB][kRegMaxK];
+    constexpr int SR = kMaxSel + 1;  // odd row stride: the wave's four tokens in distinct banks
+    __shared__ int sel_i[TPB][SR];
+    __shared__ float sel_s[TPB][SR];
     // each lane's first kRegStage marked chunks, copied from its registers
     // (slot-major, so a wave's copies are consecutive 16-byte units)
     __shared__ float4 staged[kRegStage][64 * WAVES];
@@ -261,19 +280,39 @@ __global__ __launch_bounds__(64 * WAVES) void select_reg_kernel(RouterArgs a, co
         }
         // chunk and lane maxima of v = s + b
         float cm[NV];
-        float m = -INFINITY;
+        float m[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) m[g] = -INFINITY;
 #pragma unroll
         for (int c = 0; c < NV; ++c) {
             const float4 b4 = *reinterpret_cast<const float4*>(bias_s + 4 * (16 * c + j));
             const float v0 = sv[c].x + b4.x, v1 = sv[c].y + b4.y, v2 = sv[c].z + b4.z, v3 = sv[c].w + b4.w;
-            cm[c] = fmaxf(fmaxf(v0, v1), fmaxf(v2, v3));
-            m = fmaxf(m, cm[c]);
+            const float v01 = fmaxf(v0, v1), v23 = fmaxf(v2, v3);
+            cm[c] = fmaxf(v01, v23);
+            if constexpr (G == 1) {
+                m[0] = fmaxf(m[0], cm[c]);
+            } else if constexpr (G == 2) {
+                m[0] = fmaxf(m[0], v01);
+                m[1] = fmaxf(m[1], v23);
+            } else {
+                m[0] = fmaxf(m[0], v0);
+                m[1] = fmaxf(m[1], v1);
+                m[2] = fmaxf(m[2], v2);
+                m[3] = fmaxf(m[3], v3);
+            }
         }
-        // tau = the K-th largest lane maximum: K distinct elements reach it, so
-        // every element of the top-K does.  Padding lanes (-inf) make tau -inf
-        // when fewer than K lanes hold real columns.
-        const int gt = row_count_greater(m, std::make_integer_sequence<int, 15>{});
-        const float tau = row_min(gt < K ? m : INFINITY);
+        // tau = the K-th largest of the row's 16 G group maxima: K distinct
+        // elements reach it, so every element of the top-K does.  Padding
+        // groups (-inf) make tau -inf when fewer than K groups hold real
+        // columns.
+        int gt[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) gt[g] = 0;
+        row_count_greater<G>(m, gt, std::make_integer_sequence<int, 16>{});
+        float low = INFINITY;
+#pragma unroll
+        for (int g = 0; g < G; ++g) low = fminf(low, gt[g] < K ? m[g] : INFINITY);
+        const float tau = row_min(low);
 
         unsigned cmask = 0;
 #pragma unroll
@@ -359,38 +398,73 @@ __global__ __launch_bounds__(64 * WAVES) void select_reg_kernel(RouterArgs a, co
         wave_sync();
 
         if (valid && j < K) {
-            const int idx = sel_i[slot][j];
-            const float w = gate_weight(&sel_s[slot][0], K, j);
-            a.idx[t * K + j] = idx;
-            a.w[t * K + j] = w;
-            atomicAdd(&hist[idx], 1);
+            // den: fp32 sum of the selected unbiased scores in rank order
+            float den = 0.0f;
+            for (int r = 0; r < K; ++r) den = den + sel_s[slot][r];
+#pragma unroll
+            for (int r = j; r < kMaxSel; r += 16) {
+                if (r < K) {
+                    const int idx = sel_i[slot][r];
+                    a.idx[t * K + r] = idx;
+                    a.w[t * K + r] = (den == 0.0f) ? 1.0f / (float)K : sel_s[slot][r] / den;
+                    atomicAdd(&hist[idx], 1);
+                }
+            }
         }
         wave_sync();
     }
     __syncthreads();
     flush_hist(hist, a.counts, E);
+    if constexpr (TAIL) {
+        __shared__ CtrlScratch csh;
+        controller_tail<1024 / (64 * WAVES)>(a.counts, E, ctrl.Ki, ctrl.Kd, ctrl.sign_mode, ctrl.center, ctrl.bias,
+                                             ctrl.e_prev, ctrl.step, ctrl.status, ctrl.stats, ctrl.ticket, csh);
+    }
 }
 
-// Workgroup shape: waves per workgroup and resident workgroups per CU.  Every
-// workgroup flushes its histogram with one device atomic per non-zero bin, so
-// fewer, larger workgroups issue fewer atomics.
+// Workgroup shape.  Every workgroup flushes its histogram with one device
+// atomic per non-zero bin, so fewer, larger workgroups issue fewer atomics;
+// batches that would leave CUs without one use small workgroups instead.
 constexpr int kRegWaves = 16;
-constexpr int kRegWgPerCu = 1;
+constexpr int kRegSmallWaves = 4;
 
-template <int NV>
-hipError_t launch_select_reg(const RouterArgs& a, const float* scores, hipStream_t stream) {
-    constexpr int TPB = 4 * kRegWaves;
+template <int NV, int WAVES, int G>
+hipError_t launch_select_waves(const RouterArgs& a, const float* scores, const CtrlArgs& ctrl, int cus,
+                               hipStream_t stream) {
+    constexpr int TPB = 4 * WAVES;
     const int64_t ntiles = (a.T + TPB - 1) / TPB;
+    // one round of workgroups over the CUs; more tiles are walked grid-stride
+    const int64_t cap = (int64_t)cus * (kRegWaves / WAVES);
+    const int grid = (int)(ntiles < cap ? ntiles : cap);
+    if (ctrl.ticket)
+        hipLaunchKernelGGL((select_reg_kernel<NV, WAVES, G, true>), dim3(grid), dim3(64 * WAVES), 0, stream, a, scores,
+                           ctrl);
+    else
+        hipLaunchKernelGGL((select_reg_kernel<NV, WAVES, G, false>), dim3(grid), dim3(64 * WAVES), 0, stream, a,
+                           scores, ctrl);
+    return hipGetLastError();
+}
+
+template <int NV, int G>
+hipError_t launch_select_reg(const RouterArgs& a, const float* scores, const CtrlArgs& ctrl, hipStream_t stream) {
     int cus = 0;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         cus = 256;
-    // one round of workgroups over the CUs; more tiles are walked grid-stride
-    const int64_t cap = (int64_t)cus * kRegWgPerCu;
-    const int grid = (int)(ntiles < cap ? ntiles : cap);
-    hipLaunchKernelGGL((select_reg_kernel<NV, kRegWaves>), dim3(grid), dim3(64 * kRegWaves), 0, stream, a, scores);
-    return hipGetLastError();
+    if (a.T <= (int64_t)cus * 4 * kRegSmallWaves)
+        return launch_select_waves<NV, kRegSmallWaves, G>(a, scores, ctrl, cus, stream);
+    return launch_select_waves<NV, kRegWaves, G>(a, scores, ctrl, cus, stream);
+}
+
+template <int G>
+hipError_t launch_select_groups(const RouterArgs& a, const float* scores, const CtrlArgs& ctrl, hipStream_t stream) {
+    if (a.E <= 64) return launch_select_reg<1, G>(a, scores, ctrl, stream);
+    if (a.E <= 128) return launch_select_reg<2, G>(a, scores, ctrl, stream);
+    if (a.E <= 256) return launch_select_reg<4, G>(a, scores, ctrl, stream);
+    if (a.E <= 512) return launch_select_reg<8, G>(a, scores, ctrl, stream);
+    if (a.E <= 768) return launch_select_reg<12, G>(a, scores, ctrl, stream);
+    return launch_select_reg<16, G>(a, scores, ctrl, stream);
 }
 
 }  // namespace
@@ -403,6 +477,14 @@ hipError_t launch_fill_i32(int32_t* p, int32_t value, int64_t n, hipStream_t str
     return hipGetLastError();
 }
 
+hipError_t launch_select_step(const RouterArgs& a, const float* scores, const CtrlArgs* ctrl, hipStream_t stream) {
+    CtrlArgs c{};
+    if (ctrl) c = *ctrl;
+    if (a.K <= 10) return launch_select_groups<1>(a, scores, c, stream);
+    if (a.K <= 16) return launch_select_groups<2>(a, scores, c, stream);
+    return launch_select_groups<4>(a, scores, c, stream);
+}
+
 hipError_t launch_select_from_scores(const float* scores, const float* bias, int64_t T, int E, int K, int32_t* idx,
                                      float* w, int32_t* counts, hipStream_t stream) {
     RouterArgs a{};
@@ -413,12 +495,9 @@ hipError_t launch_select_from_scores(const float* scores, const float* bias, int
     a.idx = idx;
     a.w = w;
     a.counts = counts;
-    if (K <= kRegMaxK && E % 4 == 0 && (reinterpret_cast<uintptr_t>(scores) & 15) == 0) {
-        if (E <= 256) return launch_select_reg<4>(a, scores, stream);
-        if (E <= 512) return launch_select_reg<8>(a, scores, stream);
-        if (E <= 768) return launch_select_reg<12>(a, scores, stream);
-        return launch_select_reg<16>(a, scores, stream);
-    }
+    // 16-byte pieces need aligned rows
+    if (E % 4 == 0 && (reinterpret_cast<uintptr_t>(scores) & 15) == 0)
+        return launch_select_step(a, scores, nullptr, stream);
     if (E <= 256) return launch_select_be<256>(a, scores, stream);
     if (E <= 512) return launch_select_be<512>(a, scores, stream);
     if (E <= 768) return launch_select_be<768>(a, scores, stream);

@@ -8,10 +8,12 @@ scores.
 """
 import numpy as np
 import pytest
+import torch
 
 from paper_2609_39137_amd import binding as B
 from paper_2609_39137_amd import synth
-from tests.test_gpu_router import check_invariants, gpu_select, run_router
+from paper_2609_39137_amd.pipeline import RouterStep
+from tests.test_gpu_router import DEV, check_invariants, gpu_select, run_router, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -60,3 +62,62 @@ def test_a_token_s_outputs_do_not_depend_on_its_batch(T, E, K):
         np.testing.assert_array_equal(small[i].view(np.uint32), large[i][:T].view(np.uint32))
     si, sw, sc = gpu_select(large[3], b, K)
     equal(large[:3], (si, sw, sc))
+
+
+# the scored path (variant 0: small batches, large K, row-major router matrices)
+# against the fused tiling of the same order, bit for bit: scores, selection,
+# counts over two microbatches, and the controller update; (T, d, E, K, dtype):
+# both MFMA shapes and fp32, every tile size, part tiles, fewer chunks than are
+# prefetched, odd chunk counts, padded expert blocks, every number of selection
+# groups, both sizes of selection workgroups, a packed-first row-major matrix
+SCORED = [(1, 64, 32, 32, "bf16"), (16, 128, 768, 10, "bf16"), (17, 576, 384, 13, "bf16"),
+          (257, 64, 768, 16, "bf16"), (1025, 448, 768, 10, "bf16"), (2100, 64, 768, 24, "bf16"),
+          (4097, 64, 768, 20, "bf16"), (14500, 64, 768, 17, "bf16"), (33, 64, 64, 4, "bf16"),
+          (777, 256, 256, 8, "bf16"), (1500, 192, 1024, 16, "bf16"), (700, 128, 640, 11, "bf16"),
+          (4100, 64, 1024, 32, "bf16"), (5000, 64, 512, 3, "bf16"), (31, 32, 64, 4, "f32"), (1000, 288, 128, 21, "f32"),
+          (4096, 256, 64, 1, "f32")]
+
+
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("T,d,E,K,dtype", SCORED)
+@pytest.mark.parametrize("ties", [False, True])
+def test_scored_path_equals_the_fused_tiling(T, d, E, K, dtype, packed, ties):
+    x, W = synth.normal_router_inputs(T, d, E, seed=T + K, dtype=dtype, w_std=0.05)
+    if ties:  # equal rows: lists that overflow, ranks decided by the index
+        W[: E // 2] = W[0]
+    code = B.IDB_DTYPE_BF16 if dtype == "bf16" else B.IDB_DTYPE_F32
+    xt, Wt = to_dev(x), to_dev(W)
+    fused = B.idb_router_variant_info(T, d, E, K, code, 0)["variant"]
+    outs = []
+    for variant in (0, fused):
+        rs = RouterStep(T, d, E, K, xt.dtype, B.ControllerCfg(E), variant=variant)
+        rs.state.bias.copy_(torch.from_numpy(synth.bias(E, "zero" if ties else "small", seed=K)))
+        Wa = None if packed else Wt
+        if packed:
+            rs.pack(Wt)
+        dump = torch.full((T, E), -1.0, dtype=torch.float32, device=DEV)
+        rs.route(xt, Wa, scores_dump=dump)
+        got = [dump.clone(), rs.idx.clone(), rs.w.clone(), rs.counts.clone()]
+        rs.step(xt, Wa)
+        rs.step(xt, Wa, accumulate=True)
+        got += [t.clone() for t in (rs.idx, rs.w, rs.counts, rs.state.bias, rs.state.e_prev, rs.state.step,
+                                    rs.state.status, rs.stats)]
+        outs.append([t.cpu().numpy() for t in got])
+    for a, g in zip(*outs):
+        np.testing.assert_array_equal(a.view(np.uint32), g.view(np.uint32))
+
+
+def test_a_workspace_sized_for_the_fused_tiling_keeps_it():
+    # a caller that sized its workspace by the fused tiling (or passes none to
+    # a one-slice tiling) is served as before, with the same outputs
+    for T, E, K, ws_bytes in ((300, 768, 10, 3 * (300 * 2 * 10 * 4 + 255) // 256 * 256 + 1024), (300, 256, 8, 0)):
+        x, W = synth.normal_router_inputs(T, 128, E, seed=T, w_std=0.05)
+        want = run_router(x, W, synth.bias(E, "small", seed=1), K, dump=False)
+        assert B.idb_router_workspace_bytes(T, 128, E, K, B.IDB_DTYPE_BF16, 0) > ws_bytes
+        idx = torch.empty((T, K), dtype=torch.int32, device=DEV)
+        w = torch.empty((T, K), dtype=torch.float32, device=DEV)
+        c = torch.empty(E, dtype=torch.int32, device=DEV)
+        ws = torch.empty(ws_bytes, dtype=torch.uint8, device=DEV) if ws_bytes else None
+        B.idb_router_forward(to_dev(x), to_dev(W), torch.from_numpy(synth.bias(E, "small", seed=1)).to(DEV), K, idx, w,
+                             c, workspace=ws)
+        equal([idx.cpu().numpy(), w.cpu().numpy(), c.cpu().numpy()], want[:3])
