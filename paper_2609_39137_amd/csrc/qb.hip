@@ -7,15 +7,17 @@
 // s comes expert-major ([E][T], written by the router in its Quantile
 // Balancing mode) and alpha [T] is each token's (K+1)-th largest biased score.
 //
-// One workgroup per expert finds the exact k-th smallest margin by an
-// MSB-first radix select over the margins' order-preserving 32-bit keys: four
-// passes of 8-bit digits, each a histogram of the keys that match the digits
-// found so far (one LDS histogram per wave, then summed), the digit taken
-// where the running count reaches the rank still wanted.  Up to 32768 tokens
-// each thread keeps its keys in registers (R <= 32 of them, 512 or 1024
-// threads) and the selection first narrows the keys to the few near the top
-// (see qb_update_reg_kernel).  Beyond 32768 tokens each pass recomputes the
-// keys from global memory.
+// One workgroup per expert finds the exact k-th smallest margin over the
+// margins' order-preserving 32-bit keys.  Up to 65536 tokens each thread keeps
+// its keys in registers (R <= 64 of them, 512 or 1024 threads; one read of the
+// row at any 4-byte alignment) and a sampled bracket narrows them to a short
+// list (qb_update_reg_kernel).  Measured at T = 16384, E = 768, K = 10: 19.7 us
+// (2.6 TB/s; 22.0 us with a threshold from the per-thread maxima, which also
+// needed a full radix select from r = T K / E > 512 or 1024 on), at T = 50001,
+// E = 256, K = 8: 30.0 us (1.7 TB/s; 145 us recomputing the keys in four radix
+// passes).  Shorter than one piece or longer rows take an MSB-first radix
+// select with the keys recomputed from global memory in each of four passes of
+// 8-bit digits.
 //
 // With a counts pointer, workgroup 0 also writes MaxVio/MinVio of the step's
 // counts (Eq. vio), as the stand-alone statistics kernel does: exact integer
@@ -32,7 +34,7 @@ namespace idb {
 namespace {
 
 constexpr int kQbThreads = 512;  // the global-memory kernel's workgroup
-constexpr int kQbList = 4096;    // compacted keys after the first pass
+constexpr int kQbList = 4096;    // listed keys of a 512-thread workgroup
 
 // Order-preserving key of a float (after -0 -> +0): a < b iff key(a) < key(b).
 __device__ __forceinline__ unsigned order_key(float d) {
@@ -287,141 +289,210 @@ __device__ __forceinline__ void qb_stats_load(const int32_t* __restrict__ counts
     }
 }
 
-// NT threads, R keys per thread in registers (T <= R * NT).  The wanted key
-// is the r-th largest, r = T - k + 1, normally far fewer than T.  When r <=
-// NT: tau = the r-th largest of the threads' maxima with its 16 low bits
-// cleared (at least r keys are >= tau, so the wanted key is one of them, and
-// its rank from the top is the same within the keys >= tau); those keys go to
-// an LDS list and one wave selects the exact key from it (both small
-// selections run in one wave on registers; a longer list is read from LDS
-// each pass).  Otherwise, or when the list would overflow, a full radix
-// select over the registers.
-template <int NT, int R, bool VEC>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 ? 6 : 1)))
-void qb_update_reg_kernel(const float* __restrict__ scores_t,
-                                                           const float* __restrict__ alpha, int64_t T, int E, int K,
-                                                           float rho, float* __restrict__ bias,
-                                                           const int32_t* __restrict__ counts,
-                                                           double* __restrict__ stats) {
+// Four floats at any 4-byte aligned address (rows of odd length).
+struct __attribute__((packed, aligned(4))) f4u {
+    float v[4];
+};
+
+// NT threads, R keys per thread in registers (4 <= T <= R * NT): one read of
+// the row.  The wanted key is the r-th largest, r = T - k + 1.
+//   1. A sample of one key per thread, spread over the row, brackets it: the
+//      sample's order statistics 4 standard deviations above and below the
+//      expected rank, from a 16-bit radix select by one wave each (rounded
+//      outwards), give [lo, hi].
+//   2. The keys above hi are counted, those in [lo, hi] go to an LDS list
+//      (about T sqrt(r/T) / 4 of them at NT = 1024; 540 at T = 16384, r = 213).
+//   3. The list's histogram over 1024 equal key intervals gives the interval of
+//      the wanted rank; its few keys are ranked by counting.
+// When the bracket misses (the sample does not bind the row), the list
+// overflows, or an interval holds too many keys (ties), a radix select over
+// the list or the registers takes over: the result is exact in every case.
+// Bound by reading the row, then by the barriers of the three steps.
+template <int NT, int R>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 ? 6 : 4)))
+void qb_update_reg_kernel(const float* __restrict__ scores_t, const float* __restrict__ alpha, int64_t T64, int E,
+                          int K, float rho, float* __restrict__ bias, const int32_t* __restrict__ counts,
+                          double* __restrict__ stats) {
     constexpr int NW = NT / 64;
     constexpr int NQ = (1024 + NT - 1) / NT;  // counts per thread of workgroup 0 (E <= 1024)
+    constexpr int Q = R / 4;
+    constexpr int BQ = Q < 4 ? Q : 4;  // pieces in flight per batch
+    constexpr int BINS = 1024;
+    constexpr unsigned LIST = NT == 1024 ? 8192 : kQbList;
+    static_assert(NW * 256 >= BINS, "the interval histogram shares the radix histograms' memory");
     __shared__ unsigned hist[NW][256];
-    __shared__ unsigned list[kQbList];
-    __shared__ unsigned maxima[NT];
-    __shared__ unsigned pick[3];  // digit, keys below it, keys in it
-    __shared__ unsigned nlist, tau_s;
+    __shared__ unsigned list[LIST];
+    __shared__ unsigned sample[NT];  // then the wanted interval's keys
+    __shared__ unsigned pick[3];
+    __shared__ unsigned nlist, nabove, nsmall, lo_s, hi_s, result_s;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int j = blockIdx.x;
+    const int T = (int)T64;
     const float* row = scores_t + (int64_t)j * T;
     const bool with_stats = counts && j == 0;  // uniform over the workgroup
 
-    // Key slot r holds token tok(r): with VEC (T % 4 == 0) the tokens
-    // 4 (tid + NT i) + c for r = 4 i + c, read as float4 pieces, every load of
-    // the thread in flight at once; else tid + NT r.  Slots past T are never
-    // counted.
+    // Piece p = tid + NT i holds tokens 4p .. 4p + 3; the row's last piece ends
+    // at its last token and drops the tokens of the piece before it.  Slots
+    // without a token hold key 0, below every key of a number.
     unsigned key[R];
-    auto tok = [&](int r) -> int64_t {
-        return VEC ? 4 * (tid + (int64_t)(r / 4) * NT) + (r % 4) : tid + (int64_t)r * NT;
-    };
-    if (VEC) {
-        constexpr int Q = R / 4;
-        const float4* row4 = reinterpret_cast<const float4*>(row);
-        const float4* alpha4 = reinterpret_cast<const float4*>(alpha);
-        const int64_t last = T / 4 - 1;
-        float4 sv[Q], av[Q];
+    const int pieces = (T + 3) / 4;
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            int64_t q = tid + (int64_t)i * NT;
-            q = q < last ? q : last;
-            sv[i] = row4[q];
-            av[i] = alpha4[q];
+    for (int b = 0; b < Q; b += BQ) {
+        f4u sv[BQ], av[BQ];
+#pragma unroll
+        for (int i = 0; i < BQ; ++i) {
+            const int p = tid + (b + i) * NT;
+            int t0 = 4 * (p < pieces ? p : pieces - 1);
+            t0 = t0 < T - 4 ? t0 : T - 4;
+            sv[i] = *reinterpret_cast<const f4u*>(row + t0);
+            av[i] = *reinterpret_cast<const f4u*>(alpha + t0);
         }
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            key[4 * i + 0] = order_key(sv[i].x - av[i].x);
-            key[4 * i + 1] = order_key(sv[i].y - av[i].y);
-            key[4 * i + 2] = order_key(sv[i].z - av[i].z);
-            key[4 * i + 3] = order_key(sv[i].w - av[i].w);
-        }
-    } else {
-        constexpr int H = R < 16 ? R : 16;  // loads in flight per batch
+        for (int i = 0; i < BQ; ++i) {
 #pragma unroll
-        for (int h = 0; h < R; h += H) {
-            float sv[H], av[H];
+            for (int c = 0; c < 4; ++c) key[4 * (b + i) + c] = order_key(sv[i].v[c] - av[i].v[c]);
+            const int p = tid + (b + i) * NT;
+            if (4 * p + 4 > T) {
+                const int skip = p < pieces ? 4 * p + 4 - T : 4;  // leading slots without a token of their own
 #pragma unroll
-            for (int r = 0; r < H; ++r) {
-                int64_t t = tid + (int64_t)(h + r) * NT;
-                t = t < T ? t : T - 1;
-                sv[r] = row[t];
-                av[r] = alpha[t];
+                for (int c = 0; c < 4; ++c)
+                    if (c < skip) key[4 * (b + i) + c] = 0u;
             }
-#pragma unroll
-            for (int r = 0; r < H; ++r) key[h + r] = order_key(sv[r] - av[r]);
         }
     }
-    auto live = [&](int r) { return tok(r) < T; };
 
-    const unsigned k = (unsigned)((T * (int64_t)(E - K) + E - 1) / E);  // 1-based ascending rank
-    const unsigned r_top = (unsigned)T - k + 1u;                       // the same key's rank from the top
-    const int64_t holders = VEC ? (T + 3) / 4 : T;                      // threads holding at least one key
-    const unsigned nvalid = (unsigned)(holders < NT ? holders : NT);
-    bool done = false;
-    unsigned result = 0u;
-    if (r_top <= nvalid) {
-        unsigned m = 0u;
+    const unsigned k = (unsigned)((T64 * (int64_t)(E - K) + E - 1) / E);  // 1-based ascending rank
+    const unsigned r_top = (unsigned)T - k + 1u;                         // the same key's rank from the top
+    if (tid == 0) {
+        nlist = 0u;
+        nabove = 0u;
+        nsmall = 0u;
+        lo_s = 1u;
+        hi_s = ~0u;
+    }
+    if ((unsigned)T > LIST / 2) {  // else the whole row goes to the list
+        // 1. the bracket; only slots that hold a token of every thread sampled
+        const int full = T / (4 * NT);  // whole rounds of pieces
+        const int slot = full > 0 ? tid % (4 * full) : 3;
+        const int ns = pieces < NT ? pieces : NT;
+        unsigned mine = 0u;
+#pragma unroll
+        for (int r = 0; r < R; ++r) mine = r == slot ? key[r] : mine;
+        sample[tid] = mine;
+        __syncthreads();
+        const float share = (float)r_top / (float)T;
+        const float mid = share * (float)ns, dev = 4.0f * sqrtf(mid * (1.0f - share)) + 1.0f;
+        const int hi_rank = (int)(mid - dev), lo_rank = (int)(mid + dev) + 1;  // from the top
+        if (wave == 0 && lo_rank <= ns) {
+            const unsigned v = wave_select_reg<NT / 64, 16>(sample, (unsigned)ns, (unsigned)(ns - lo_rank + 1),
+                                                            hist[0]);
+            if (lane == 0 && v > 1u) lo_s = v;
+        }
+        if (wave == 1 && hi_rank >= 1) {
+            const unsigned v = wave_select_reg<NT / 64, 16>(sample, (unsigned)ns, (unsigned)(ns - hi_rank + 1),
+                                                            hist[1]);
+            if (lane == 0) hi_s = v | 0xffffu;
+        }
+    }
+    __syncthreads();
+    const unsigned lo = lo_s, hi = hi_s;
+    // 2. counts above and inside, packed for one scan over the wave; one LDS
+    // atomic per wave for its place in the list
+    unsigned c = 0u;
+#pragma unroll
+    for (int r = 0; r < R; ++r) c += key[r] > hi ? 0x10000u : key[r] >= lo ? 1u : 0u;
+    unsigned incl = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned up = __shfl_up(incl, o);
+        if (lane >= o) incl += up;
+    }
+    unsigned base = 0u;
+    if (lane == 63) {
+        base = atomicAdd(&nlist, incl & 0xffffu);
+        atomicAdd(&nabove, incl >> 16);
+    }
+    unsigned pos = __shfl(base, 63) + (incl & 0xffffu) - (c & 0xffffu);
+    if ((c & 0xffffu) != 0u) {
 #pragma unroll
         for (int r = 0; r < R; ++r)
-            if (live(r)) m = key[r] > m ? key[r] : m;
-        maxima[tid] = m;  // meaningful for tid < nvalid
-        if (tid == 0) nlist = 0u;
-        __syncthreads();
-        if (wave == 0) {
-            // 16 high bits suffice: a lower bound of the r-th largest maximum
-            const unsigned t = wave_select_reg<NT / 64, 16>(maxima, nvalid, nvalid - r_top + 1u, hist[0]);
-            if (lane == 0) tau_s = t;
-        }
-        __syncthreads();
-        const unsigned tau = tau_s;
-        // the keys >= tau into the list: counts, a scan over the wave, one
-        // LDS atomic per wave for its base
-        unsigned c = 0u;
-#pragma unroll
-        for (int r = 0; r < R; ++r) c += (live(r) && key[r] >= tau) ? 1u : 0u;
-        unsigned incl = c;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const unsigned up = __shfl_up(incl, o);
-            if (lane >= o) incl += up;
-        }
-        unsigned base = 0u;
-        if (lane == 63) base = atomicAdd(&nlist, incl);
-        unsigned pos = __shfl(base, 63) + incl - c;
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (live(r) && key[r] >= tau) {
-                if (pos < (unsigned)kQbList) list[pos] = key[r];
+            if (key[r] >= lo && key[r] <= hi) {
+                if (pos < LIST) list[pos] = key[r];
                 ++pos;
             }
-        __syncthreads();
-        const unsigned n = nlist;
-        if (n <= (unsigned)NT) {
-            if (wave == 0) {
-                result = wave_select_reg<NT / 64>(list, n, n - r_top + 1u, hist[0]);
-                if (lane == 0) write_bias(bias, j, result, rho);
-            }
-            done = true;
-        } else if (n <= (unsigned)kQbList) {
-            if (wave == 0) {
-                result = wave_select(list, n, n - r_top + 1u, hist[0]);
-                if (lane == 0) write_bias(bias, j, result, rho);
-            }
-            done = true;
-        }
     }
-    if (!done) {
-        // full radix select over the registers
-        unsigned kleft = k, prefix = 0u, mask = 0u;
+    unsigned* bins = &hist[0][0];
+    for (int i = tid; i < BINS; i += NT) bins[i] = 0u;
+    __syncthreads();
+    const unsigned n = nlist, above = nabove;
+    if (above < r_top && r_top <= above + n && n <= LIST) {
+        // 3. intervals of 2^sh keys from lo
+        const unsigned want = r_top - above;  // rank from the top of the list
+        const unsigned span = hi - lo;
+        const int sh = span < (unsigned)BINS ? 0 : 22 - __builtin_clz(span);
+        for (unsigned i = tid; i < n; i += NT) atomicAdd(&bins[(list[i] - lo) >> sh], 1u);
+        __syncthreads();
+        if (wave == 0) {
+            // lane l owns the 16 bins below BINS - 16 l
+            const unsigned* own = bins + BINS - 16 * (lane + 1);
+            unsigned cnt[16], tot = 0u;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                cnt[i] = own[i];
+                tot += cnt[i];
+            }
+            unsigned sum = tot;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const unsigned up = __shfl_up(sum, o);
+                if (lane >= o) sum += up;
+            }
+            unsigned run = sum - tot;
+            if (run < want && want <= sum) {
+#pragma unroll
+                for (int i = 15; i >= 0; --i) {
+                    if (run < want && want <= run + cnt[i]) {
+                        pick[0] = (unsigned)(BINS - 16 * (lane + 1) + i);
+                        pick[1] = run;
+                        pick[2] = cnt[i];
+                    }
+                    run += cnt[i];
+                }
+            }
+        }
+        __syncthreads();
+        const unsigned bin = pick[0], m = pick[2], left = want - pick[1];
+        if (m <= (unsigned)NT) {
+            for (unsigned i = tid; i < n; i += NT) {
+                const unsigned u = list[i];
+                if ((u - lo) >> sh == bin) sample[atomicAdd(&nsmall, 1u)] = u;
+            }
+            __syncthreads();
+            // every thread ranks one key: the wanted one has fewer than
+            // `left` keys above it and at least `left` not below it
+            if (tid < (int)m) {
+                const unsigned u = sample[tid];
+                unsigned gt = 0u, ge = 0u;
+                for (unsigned i = 0; i < m; ++i) {
+                    const unsigned o = sample[i];
+                    gt += o > u ? 1u : 0u;
+                    ge += o >= u ? 1u : 0u;
+                }
+                if (gt < left && left <= ge) result_s = u;  // equal keys write the same value
+            }
+            __syncthreads();
+        } else {
+            if (wave == 0) {
+                const unsigned u = wave_select(list, n, n - want + 1u, hist[0]);
+                if (lane == 0) result_s = u;
+            }
+            __syncthreads();
+        }
+        if (tid == 0) write_bias(bias, j, result_s, rho);
+    } else {
+        // full radix select over the registers; the empty slots rank lowest
+        unsigned kleft = k + (unsigned)(R * NT - T), prefix = 0u, mask = 0u;
         for (int shift = 24; shift >= 0; shift -= 8) {
             __syncthreads();
             for (int i = tid; i < NW * 256; i += NT) (&hist[0][0])[i] = 0u;
@@ -429,7 +500,7 @@ void qb_update_reg_kernel(const float* __restrict__ scores_t,
             DigitCounter dc;
 #pragma unroll
             for (int r = 0; r < R; ++r)
-                if (live(r) && (key[r] & mask) == prefix) dc.add(hist[wave], (key[r] >> shift) & 255u);
+                if ((key[r] & mask) == prefix) dc.add(hist[wave], (key[r] >> shift) & 255u);
             dc.flush(hist[wave]);
             __syncthreads();
             if (wave == 0) pick_digit(hist, kleft, pick);
@@ -438,8 +509,7 @@ void qb_update_reg_kernel(const float* __restrict__ scores_t,
             mask |= 255u << shift;
             kleft -= pick[1];
         }
-        result = prefix;
-        if (tid == 0) write_bias(bias, j, result, rho);
+        if (tid == 0) write_bias(bias, j, prefix, rho);
     }
     if (with_stats) {
         int cnt[NQ];
@@ -492,30 +562,28 @@ __global__ __launch_bounds__(kQbThreads) void qb_update_global_kernel(const floa
 template <int NT, int R>
 void launch_reg(const float* scores_t, const float* alpha, int64_t T, int E, int K, float rho, float* bias,
                 const int32_t* counts, double* stats, hipStream_t stream) {
-    // float4 pieces need T % 4 == 0 (16-byte aligned rows) and aligned buffers
-    const bool vec = (T % 4 == 0) && ((reinterpret_cast<uintptr_t>(scores_t) | reinterpret_cast<uintptr_t>(alpha)) &
-                                      15) == 0;
-    if (vec)
-        hipLaunchKernelGGL((qb_update_reg_kernel<NT, R, true>), dim3((unsigned)E), dim3(NT), 0, stream, scores_t,
-                           alpha, T, E, K, rho, bias, counts, stats);
-    else
-        hipLaunchKernelGGL((qb_update_reg_kernel<NT, R, false>), dim3((unsigned)E), dim3(NT), 0, stream, scores_t,
-                           alpha, T, E, K, rho, bias, counts, stats);
+    hipLaunchKernelGGL((qb_update_reg_kernel<NT, R>), dim3((unsigned)E), dim3(NT), 0, stream, scores_t, alpha, T, E, K,
+                       rho, bias, counts, stats);
 }
 
 }  // namespace
 
 hipError_t launch_qb_update(const float* scores_t, const float* alpha, int64_t T, int E, int K, float rho,
                             float* bias, const int32_t* counts, double* stats, hipStream_t stream) {
-    if (T <= 16 * 512)
+    // 512 threads while the row fits 32 keys per thread (three workgroups per
+    // CU), then 1024 with up to 64; longer rows, and rows shorter than one
+    // piece, are read again in every radix pass
+    if (T < 4 || T > 64 * 1024)
+        hipLaunchKernelGGL(qb_update_global_kernel, dim3((unsigned)E), dim3(kQbThreads), 0, stream, scores_t, alpha,
+                           T, E, K, rho, bias, counts, stats);
+    else if (T <= 16 * 512)
         launch_reg<512, 16>(scores_t, alpha, T, E, K, rho, bias, counts, stats, stream);
     else if (T <= 32 * 512)
         launch_reg<512, 32>(scores_t, alpha, T, E, K, rho, bias, counts, stats, stream);
     else if (T <= 32 * 1024)
         launch_reg<1024, 32>(scores_t, alpha, T, E, K, rho, bias, counts, stats, stream);
     else
-        hipLaunchKernelGGL(qb_update_global_kernel, dim3((unsigned)E), dim3(kQbThreads), 0, stream, scores_t, alpha,
-                           T, E, K, rho, bias, counts, stats);
+        launch_reg<1024, 64>(scores_t, alpha, T, E, K, rho, bias, counts, stats, stream);
     return hipGetLastError();
 }
 

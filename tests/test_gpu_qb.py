@@ -178,3 +178,44 @@ def test_qb_closed_loop():
         flips += int((np.sort(idx, 1) != np.sort(r_idx, 1)).any(1).sum())
         np.testing.assert_allclose(rs.state.bias.cpu().numpy(), ref_b, atol=1e-4, err_msg=f"oracle bias step {t}")
     assert flips <= 0.01 * T * 6, flips
+
+
+def qb_case(T, E, kind):
+    """Scores [T][E] whose rows make the sampled bracket bind, miss or hold many ties."""
+    rng = np.random.default_rng(T + E)
+    s = synth.scores(T, E, "beta", seed=T).copy()
+    if kind == "sorted":      # tokens in ascending order of every expert's score
+        s.sort(axis=0)
+    elif kind == "block":     # a few high scores, all in one run of tokens
+        s *= np.float32(0.25)
+        n = max(1, T // 50)
+        s[T // 3: T // 3 + n] += np.float32(0.5)
+    elif kind == "constant":  # every margin of an expert equal
+        s[:] = s[0]
+    elif kind == "levels":    # a handful of values
+        s = (rng.integers(0, 5, (T, E)) / np.float32(8.0)).astype(np.float32)
+    return s
+
+
+# row lengths around the pieces of four tokens, the whole-row list, the keys
+# per thread of each kernel form (8192, 16384, 32768 and 65536 tokens) and the
+# form beyond them; ranks from T / 96 to T / 2
+@pytest.mark.parametrize("T,E,K", [(3, 32, 4), (4, 32, 4), (5, 32, 16), (7, 96, 1), (2048, 32, 8), (2049, 32, 8),
+                                   (8191, 32, 16), (8193, 64, 1), (16383, 32, 2), (16385, 32, 8), (32769, 8, 4),
+                                   (50001, 32, 1), (65535, 16, 2), (65536, 8, 4), (65537, 8, 2)])
+@pytest.mark.parametrize("kind", ["beta", "sorted", "block", "constant", "levels"])
+def test_qb_update_row_lengths_and_brackets(T, E, K, kind):
+    s = qb_case(T, E, kind)
+    b = synth.bias(E, "small", seed=E)
+    alpha = oracle.qb_alpha(s, b, K)
+    for rho in (0.0, 0.5):
+        want = oracle.qb_update(s, alpha, K, rho, b.copy())
+        # rows and cutoffs at addresses that are multiples of 4 bytes only
+        buf = torch.empty(T * E + 1, dtype=torch.float32, device=DEV)
+        st = buf[1:].view(E, T)
+        st.copy_(torch.from_numpy(np.ascontiguousarray(s.T)))
+        abuf = torch.empty(T + 1, dtype=torch.float32, device=DEV)
+        abuf[1:].copy_(torch.from_numpy(alpha))
+        bt = torch.from_numpy(b.copy()).to(DEV)
+        B.idb_qb_update(st, abuf[1:], K, rho, bt)
+        np.testing.assert_array_equal(bits(bt), want.view(np.uint32))
