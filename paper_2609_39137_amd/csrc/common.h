@@ -19,15 +19,9 @@ constexpr int32_t kStatusEmpty = 3;
 // Largest number of experts selected per token on the GPU paths.
 constexpr int kMaxK = 32;
 
-// Strict total order of the biased-score ranking (Eq. pid-routing) with the
-// lowest expert index winning ties: does (va, ia) rank above (vb, ib)?
-// IEEE comparisons, so -0 == +0.
-__device__ __forceinline__ bool ranks_above(float va, int ia, float vb, int ib) {
-    return (va > vb) || (va == vb && ia < ib);
-}
-
-// The same order as one unsigned 64-bit key: key(a) > key(b) exactly when
-// ranks_above(a, b).  High word: the float's bits mapped to an unsigned order
+// The order of the biased-score ranking (Eq. pid-routing: value descending,
+// lowest index first among equal values, -0 == +0) as one unsigned 64-bit key,
+// larger first.  High word: the float's bits mapped to an unsigned order
 // (after -0 -> +0, so equal values get equal words); low word: ~index, so the
 // lower index wins ties.  Key 0 ranks below every finite or infinite value and
 // serves as "no entry".
@@ -59,53 +53,21 @@ __device__ __forceinline__ float sigmoid_fast(float z) {
     return __builtin_amdgcn_rcpf(1.0f + e);
 }
 
-// 16 values held one per lane in each 16-lane row of a wave: the value of
-// rank `r` in ascending order (bitonic sort across the row).  Every lane of the
-// row gets the result.  All 16 lanes of the row must be active.
-__device__ __forceinline__ float row16_sorted_ascending_at(float x, int r) {
-    const int lane = threadIdx.x & 15;
-#pragma unroll
-    for (int k = 2; k <= 16; k <<= 1) {
-#pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            float o = __shfl_xor(x, j, 16);
-            bool lower = (lane & j) == 0;
-            bool up = (lane & k) == 0;
-            float lo = fminf(x, o), hi = fmaxf(x, o);
-            x = (lower == up) ? lo : hi;
-        }
-    }
-    return __shfl(x, r, 16);
+// x of the lane R below in the same 16-lane row (cyclic).
+template <int R>
+__device__ __forceinline__ int row_rot(int x) {
+    return __builtin_amdgcn_update_dpp(0, x, 0x120 + R, 0xF, 0xF, false);
 }
-
-// Sort N (a power of two) register values ascending in place (fixed bitonic
-// network).
-template <int N>
-__device__ __forceinline__ void sort_ascending(float (&a)[N]) {
-    static_assert((N & (N - 1)) == 0, "bitonic network needs a power of two");
-#pragma unroll
-    for (int k = 2; k <= N; k <<= 1) {
-#pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1) {
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const int l = i ^ j;
-                if (l > i) {
-                    const float lo = fminf(a[i], a[l]), hi = fmaxf(a[i], a[l]);
-                    if ((i & k) == 0) {
-                        a[i] = lo;
-                        a[l] = hi;
-                    } else {
-                        a[i] = hi;
-                        a[l] = lo;
-                    }
-                }
-            }
-        }
-    }
+template <int R>
+__device__ __forceinline__ float row_rot(float x) {
+    return __builtin_bit_cast(float, row_rot<R>(__builtin_bit_cast(int, x)));
 }
-
-__device__ __forceinline__ uint4 ld16(const void* p) { return *reinterpret_cast<const uint4*>(p); }
+template <int R>
+__device__ __forceinline__ double row_rot(double x) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const unsigned lo = (unsigned)row_rot<R>((int)(unsigned)u), hi = (unsigned)row_rot<R>((int)(unsigned)(u >> 32));
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
 
 // Raw buffer resource over [base, base + bytes) (bytes < 2^32) and a 16-byte
 // load at per-lane offset voff plus scalar offset soff.
@@ -146,15 +108,6 @@ __device__ __forceinline__ int xcd_block_order() {
     int L = blockIdx.x;
     if ((nb & 7) == 0) L = (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3);
     return L;
-}
-
-// Gate weights of one token from its selected unbiased scores in rank order:
-// den is the fp32 sum in rank order; w_r = s_r / den (IEEE division); den == 0
-// gives 1/K.
-__device__ __forceinline__ float gate_weight(const float* sel_s, int K, int r) {
-    float den = 0.0f;
-    for (int q = 0; q < K; ++q) den = den + sel_s[q];
-    return (den == 0.0f) ? 1.0f / (float)K : sel_s[r] / den;
 }
 
 }  // namespace idb

@@ -58,6 +58,38 @@ def test_layers_update_and_diagnostics_match_oracle(L, E, kind, mode, center):
             np.testing.assert_array_equal(g_diag[l], want_diag, err_msg=f"diag step {t} layer {l}")
 
 
+# pool sizes around one row, one wave and the workgroups' tree levels; counts
+# whose sums need 64 bits, equal counts at the busiest-10% threshold, zeros
+@pytest.mark.parametrize("E", [1, 2, 3, 8, 9, 15, 16, 17, 31, 33, 63, 64, 65, 127, 128, 129, 256, 257, 511, 513, 1000,
+                               1023, 1024])
+def test_update_reductions_at_every_pool_size(E):
+    rng = np.random.default_rng(E)
+    loads = np.stack([rng.integers(0, 2 ** 31, E, dtype=np.int64), rng.integers(0, 5, E), np.full(E, 2 ** 31 - 1),
+                      rng.integers(0, 2, E) * 65536 + 65535, np.where(np.arange(E) % 3 == 0, 1000, 999)])
+    loads = loads.astype(np.int32)
+    loads[1, 0] = 3  # never an empty batch
+    L = len(loads)
+    cfg = B.ControllerCfg(E)
+    many, one = B.ControllerState(E, DEV, layers=L), B.ControllerState(E, DEV)
+    refs, ref = [oracle.ControllerState(E) for _ in range(L)], oracle.ControllerState(E)
+    stats, diag = (torch.empty((L, n), dtype=torch.float64, device=DEV) for n in (2, 4))
+    single = torch.empty(2, dtype=torch.float64, device=DEV)
+    for t in range(3):
+        counts = np.roll(loads, t, axis=1).copy()
+        B.idb_controller_update_layers(torch.from_numpy(counts).to(DEV), cfg, many, stats, diag)
+        for l in range(L):
+            status, want = oracle.controller_diag(counts[l], refs[l], 6e-3, 6e-3, B.IDB_INTEGRAL_ERROR, True)
+            assert int(many.status[l].item()) == status
+            np.testing.assert_array_equal(many.bias[l].cpu().numpy().view(np.uint32), refs[l].bias.view(np.uint32))
+            np.testing.assert_array_equal(many.e_prev[l].cpu().numpy().view(np.uint32), refs[l].e_prev.view(np.uint32))
+            np.testing.assert_array_equal(stats[l].cpu().numpy(), oracle.load_stats(counts[l]))
+            np.testing.assert_array_equal(diag[l].cpu().numpy(), want)
+            B.idb_controller_step(torch.from_numpy(counts[l]).to(DEV), cfg, one, single)
+            oracle.controller(counts[l], ref, 6e-3, 6e-3)
+            np.testing.assert_array_equal(one.bias.cpu().numpy().view(np.uint32), ref.bias.view(np.uint32))
+            np.testing.assert_array_equal(single.cpu().numpy(), oracle.load_stats(counts[l]))
+
+
 def test_one_layer_equals_the_single_layer_update():
     E = 768
     cfg = B.ControllerCfg(E)
