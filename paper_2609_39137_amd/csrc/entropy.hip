@@ -22,9 +22,9 @@ namespace idb {
 
 namespace {
 
-constexpr int kEntThreads = 256;
+constexpr int kEntThreads = 512;
 constexpr int kEntWaves = kEntThreads / 64;
-constexpr int kEntPerLane = 16;  // scores per lane and token: E <= 1024
+constexpr int kEntAhead = 2;  // rows a wave has in flight
 
 __device__ inline double block_sum_fixed(double v, double* red) {
     // fixed butterfly inside each wave, then the waves in order
@@ -39,110 +39,155 @@ __device__ inline double block_sum_fixed(double v, double* red) {
     return t;
 }
 
-// c log2 c of one clamped biased score, as an fp64 term (0 for c = 0 and for
-// c below the smallest normal fp32, whose term is below 2^-119 in size).
-__device__ inline double clog2c(float c) {
-    return c >= 1.17549435e-38f ? (double)c * (double)__builtin_amdgcn_logf(c) : 0.0;
+// Four floats at any 4-byte aligned address (rows of odd length).
+struct __attribute__((packed, aligned(4))) f4u {
+    float v[4];
+};
+
+// A row's values of this lane: columns 4 (lane + 64 p) .. + 3 for p < NP
+// (256 NP >= E); `pad` past the row.
+template <int NP>
+__device__ __forceinline__ void load_row(const float* __restrict__ row, int E, float pad, float (&v)[4 * NP]) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const int c0 = 4 * (lane + 64 * p);
+        if (c0 + 4 <= E) {
+            const f4u f = *reinterpret_cast<const f4u*>(row + c0);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[4 * p + c] = f.v[c];
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[4 * p + c] = c0 + c < E ? row[c0 + c] : pad;
+        }
+    }
 }
 
-// One token's H_full over the softmax of its logits z (one wave, lane l
-// holding z_{l + 64 j}; padding lanes -inf).
-__device__ inline double softmax_entropy_wave(const float (&z)[kEntPerLane]) {
+// Sum over the wave in a fixed order, in every lane: row rotations (which
+// cost no LDS round trip), then two exchanges between the rows.
+__device__ __forceinline__ double wave_sum(double v) {
+    v += row_rot<8>(v);
+    v += row_rot<4>(v);
+    v += row_rot<2>(v);
+    v += row_rot<1>(v);
+    v += __shfl_xor(v, 16);
+    return v + __shfl_xor(v, 32);
+}
+
+// One token's sums Z = sum exp(z - M) and D = sum exp(z - M) (z - M) over its
+// logits z (one wave; padding -inf), in every lane.
+template <int N>
+__device__ __forceinline__ void softmax_sums_wave(const float (&z)[N], double& Z, double& D) {
     float m = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < kEntPerLane; ++j) m = fmaxf(m, z[j]);
+    for (int j = 0; j < N; ++j) m = fmaxf(m, z[j]);
+    m = fmaxf(m, row_rot<8>(m));
+    m = fmaxf(m, row_rot<4>(m));
+    m = fmaxf(m, row_rot<2>(m));
+    m = fmaxf(m, row_rot<1>(m));
+    m = fmaxf(m, __shfl_xor(m, 16));
+    m = fmaxf(m, __shfl_xor(m, 32));
+    Z = 0.0;
+    D = 0.0;
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    double Z = 0.0, D = 0.0;
-#pragma unroll
-    for (int j = 0; j < kEntPerLane; ++j) {
+    for (int j = 0; j < N; ++j) {
         if (z[j] != -INFINITY) {
             const float x = z[j] - m;
             const float t = __builtin_amdgcn_exp2f(x * 1.4426950408889634f);
             Z += (double)t;
-            D += (double)t * (double)x;
+            D = __builtin_fma((double)t, (double)x, D);
         }
     }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        Z += __shfl_xor(Z, o);
-        D += __shfl_xor(D, o);
-    }
-    return log(Z) - D / Z;
+    Z = wave_sum(Z);
+    D = wave_sum(D);
 }
 
+// One token's sums C = sum c and D = sum c log2 c over its clamped biased
+// scores (one wave; padding scores are 0 with bias 0), in every lane.  The
+// logarithm of a c below the smallest normal fp32 is that number's (such a term
+// is below 2^-119 in size; 0 for c = 0).
+template <int N>
+__device__ __forceinline__ void clamped_sums_wave(const float (&s)[N], const float (&b)[N], double& C, double& D) {
+    C = 0.0;
+    D = 0.0;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const float c = fmaxf(s[j] + b[j], 0.0f);
+        const double c64 = (double)c;
+        C += c64;
+        D = __builtin_fma(c64, (double)__builtin_amdgcn_logf(fmaxf(c, 1.17549435e-38f)), D);
+    }
+    C = wave_sum(C);
+    D = wave_sum(D);
+}
+
+// H_full of a token from its sums (see the head of the file).
 template <bool SOFTMAX>
+__device__ inline double entropy_of(double C, double D) {
+    constexpr double kLn2 = 0.69314718055994530942;
+    if (SOFTMAX) return log(C) - D / C;
+    return C > 0.0 ? log(C) - kLn2 * D / C : 0.0;
+}
+
+// Bound by the VALU (about 21 instructions per 64 scores, half of them fp64)
+// under the read of the scores.  A wave takes every (grid waves)-th token and
+// has two rows in flight (four: 22.3 us); only the pieces a row fills are
+// computed (NP), and the H_topK terms are spread one per thread over the
+// block's run of tokens.  At T = 16384, E = 768, K = 10: 14.4 us (3.5 TB/s;
+// 18.0 us with a logarithm and a division per token in every lane, one row
+// ahead and two shuffles per reduction step).
+template <bool SOFTMAX, int NP>
 __global__ __launch_bounds__(kEntThreads) void entropy_partial_kernel(const float* __restrict__ w, int64_t T, int K,
                                                                       const float* __restrict__ scores,
                                                                       const float* __restrict__ bias, int E,
                                                                       double* __restrict__ partial) {
     __shared__ double red[kEntWaves];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    // H_topK: one thread per token
-    double htop = 0.0;
-    for (int64_t t = (int64_t)blockIdx.x * kEntThreads + tid; t < T; t += (int64_t)gridDim.x * kEntThreads) {
-        double h = 0.0;
-        for (int r = 0; r < K; ++r) {
-            const double x = (double)w[t * K + r];
-            if (x > 0.0) h -= x * log(x);
-        }
-        htop += h;
+    const int64_t first = (int64_t)blockIdx.x * kEntWaves + wv, step = (int64_t)gridDim.x * kEntWaves;
+    constexpr float kPad = SOFTMAX ? -INFINITY : 0.0f;
+    float buf[kEntAhead][4 * NP], b[4 * NP];
+    if (scores) {
+#pragma unroll
+        for (int k = 0; k < kEntAhead; ++k)
+            if (first + k * step < T) load_row<NP>(scores + (first + k * step) * E, E, kPad, buf[k]);
+        if constexpr (!SOFTMAX) load_row<NP>(bias, E, 0.0f, b);
     }
-    const double stop = block_sum_fixed(htop, red);
-    // H_full: one wave per token, a lane's experts lane, lane + 64, ...; the
-    // bias stays in registers, and two tokens' scores are loaded at once
-    double hfull = 0.0;
-    if (SOFTMAX) {
-        // one wave per token, a lane's logits lane, lane + 64, ...
-        for (int64_t t = (int64_t)blockIdx.x * kEntWaves + wv; t < T; t += (int64_t)gridDim.x * kEntWaves) {
-            float z[kEntPerLane];
+    // H_topK: terms of the block's tokens (0 log 0 = 0)
+    const int64_t t_lo = T * blockIdx.x / gridDim.x, t_hi = T * (blockIdx.x + 1) / gridDim.x;
+    double htop = 0.0;
+    for (int64_t i = t_lo * K + tid; i < t_hi * K; i += kEntThreads) {
+        const double x = (double)w[i];
+        if (x > 0.0) htop -= x * log(x);
+    }
+    // H_full
+    double hfull = 0.0, myC = 0.0, myD = 0.0;
+    int held = 0;
+    if (scores) {
+        for (int64_t t0 = first; t0 < T; t0 += kEntAhead * step) {
 #pragma unroll
-            for (int j = 0; j < kEntPerLane; ++j) {
-                const int e = lane + 64 * j;
-                z[j] = e < E ? scores[t * E + e] : -INFINITY;
-            }
-            const double h = softmax_entropy_wave(z);
-            if (lane == 0) hfull += h;
-        }
-    } else if (scores) {
-        float b[kEntPerLane];
-#pragma unroll
-        for (int j = 0; j < kEntPerLane; ++j) b[j] = lane + 64 * j < E ? bias[lane + 64 * j] : 0.0f;
-        const int64_t step = (int64_t)gridDim.x * kEntWaves;
-        for (int64_t t0 = (int64_t)blockIdx.x * kEntWaves + wv; t0 < T; t0 += 2 * step) {
-            const int64_t t1 = t0 + step;
-            float s0[kEntPerLane], s1[kEntPerLane];
-#pragma unroll
-            for (int j = 0; j < kEntPerLane; ++j) {
-                const int e = lane + 64 * j;
-                s0[j] = e < E ? scores[t0 * E + e] : 0.0f;
-                s1[j] = (e < E && t1 < T) ? scores[t1 * E + e] : 0.0f;
-            }
-            double C0 = 0.0, D0 = 0.0, C1 = 0.0, D1 = 0.0;
-#pragma unroll
-            for (int j = 0; j < kEntPerLane; ++j) {
-                if (lane + 64 * j < E) {
-                    const float c0 = fmaxf(s0[j] + b[j], 0.0f), c1 = fmaxf(s1[j] + b[j], 0.0f);
-                    C0 += (double)c0;
-                    D0 += clog2c(c0);
-                    C1 += (double)c1;
-                    D1 += clog2c(c1);
+            for (int k = 0; k < kEntAhead; ++k) {
+                const int64_t t = t0 + k * step;
+                if (t < T) {
+                    double C, D;
+                    if constexpr (SOFTMAX) softmax_sums_wave(buf[k], C, D);
+                    else clamped_sums_wave(buf[k], b, C, D);
+                    // lane i keeps the i-th token's sums: the fp64 logarithm
+                    // and division are evaluated once per 64 tokens
+                    if (lane == held) {
+                        myC = C;
+                        myD = D;
+                    }
+                    if (++held == 64) {
+                        hfull += entropy_of<SOFTMAX>(myC, myD);
+                        held = 0;
+                    }
+                    if (t + kEntAhead * step < T) load_row<NP>(scores + (t + kEntAhead * step) * E, E, kPad, buf[k]);
                 }
             }
-#pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) {
-                C0 += __shfl_xor(C0, o);
-                D0 += __shfl_xor(D0, o);
-                C1 += __shfl_xor(C1, o);
-                D1 += __shfl_xor(D1, o);
-            }
-            constexpr double kLn2 = 0.69314718055994530942;
-            if (lane == 0) {
-                hfull += C0 > 0.0 ? log(C0) - kLn2 * D0 / C0 : 0.0;
-                if (t1 < T) hfull += C1 > 0.0 ? log(C1) - kLn2 * D1 / C1 : 0.0;
-            }
         }
+        if (lane < held) hfull += entropy_of<SOFTMAX>(myC, myD);
     }
+    const double stop = block_sum_fixed(htop, red);
     const double sfull = block_sum_fixed(hfull, red);
     if (tid == 0) {
         partial[2 * blockIdx.x] = stop;
@@ -172,16 +217,29 @@ __global__ __launch_bounds__(64) void entropy_final_kernel(const double* __restr
     }
 }
 
+template <bool SOFTMAX, int NP>
+void launch_partial(const float* gate_w, int64_t T, int K, const float* scores, const float* bias, int E,
+                    double* partial, hipStream_t stream) {
+    hipLaunchKernelGGL((entropy_partial_kernel<SOFTMAX, NP>), dim3(kEntropyBlocks), dim3(kEntThreads), 0, stream,
+                       gate_w, T, K, scores, bias, E, partial);
+}
+
 }  // namespace
 
 hipError_t launch_routing_entropy(const float* gate_w, int64_t T, int K, const float* scores, const float* bias,
                                   int E, int softmax, double* partial, double* out, hipStream_t stream) {
-    if (softmax)
-        hipLaunchKernelGGL(entropy_partial_kernel<true>, dim3(kEntropyBlocks), dim3(kEntThreads), 0, stream, gate_w,
-                           T, K, scores, bias, E, partial);
-    else
-        hipLaunchKernelGGL(entropy_partial_kernel<false>, dim3(kEntropyBlocks), dim3(kEntThreads), 0, stream, gate_w,
-                           T, K, scores, bias, E, partial);
+    const int np = (E + 255) / 256;  // 0 (no scores) to 4
+    if (softmax) {
+        if (np <= 1) launch_partial<true, 1>(gate_w, T, K, scores, bias, E, partial, stream);
+        else if (np == 2) launch_partial<true, 2>(gate_w, T, K, scores, bias, E, partial, stream);
+        else if (np == 3) launch_partial<true, 3>(gate_w, T, K, scores, bias, E, partial, stream);
+        else launch_partial<true, 4>(gate_w, T, K, scores, bias, E, partial, stream);
+    } else {
+        if (np <= 1) launch_partial<false, 1>(gate_w, T, K, scores, bias, E, partial, stream);
+        else if (np == 2) launch_partial<false, 2>(gate_w, T, K, scores, bias, E, partial, stream);
+        else if (np == 3) launch_partial<false, 3>(gate_w, T, K, scores, bias, E, partial, stream);
+        else launch_partial<false, 4>(gate_w, T, K, scores, bias, E, partial, stream);
+    }
     hipLaunchKernelGGL(entropy_final_kernel, dim3(1), dim3(64), 0, stream, partial, kEntropyBlocks, T,
                        scores ? 1 : 0, out);
     return hipGetLastError();

@@ -158,3 +158,31 @@ def test_softmax_routing_entropy_matches_oracle(T, E, K, scale):
     tol = per_token.mean() + 1e-12
     want = oracle.softmax_entropy(z)
     assert abs(got[1] - want) <= tol, (got[1], want, tol)
+
+
+# rows of every length modulo the 16-byte pieces and the pieces per lane, rows
+# at 4-byte alignment, one token, more tokens than a wave holds sums for (64 of
+# the grid's 4096 waves)
+@pytest.mark.parametrize("T,E,K", [(1, 1, 1), (5, 3, 2), (4097, 255, 3), (700, 257, 5), (333, 513, 8), (129, 769, 10),
+                                   (64, 1023, 32), (262145 + 7, 6, 2)])
+def test_routing_entropies_at_every_row_length(T, E, K):
+    r = synth.rng(T, E, K, 9)
+    w = r.random((T, K)).astype(np.float32) + np.float32(1e-3)
+    w = (w / w.sum(axis=1, keepdims=True)).astype(np.float32)
+    s = r.random((T, E)).astype(np.float32)
+    b = synth.bias(E, "small", seed=E)
+    buf = torch.empty(T * E + 1, dtype=torch.float32, device=DEV)
+    st = buf[1:].view(T, E)
+    st.copy_(torch.from_numpy(s))
+    out = torch.empty(2, dtype=torch.float64, device=DEV)
+    wt = torch.from_numpy(w).to(DEV)
+    B.idb_routing_entropy(wt, out, st, torch.from_numpy(b).to(DEV))
+    got = out.cpu().numpy()
+    # 1e-12: fp64 sums; 2^-21 (1 + log2 E + 8): the fp32 log2 of values down to 2^-8 of the mean (the module notes)
+    np.testing.assert_allclose(got[0], oracle.topk_entropy(w), rtol=1e-9, atol=1e-12)
+    assert abs(got[1] - oracle.full_entropy(s, b)) <= np.log(2.0) * 2.0 ** -21 * (9.0 + np.log2(E)) + 1e-12
+    st.copy_(torch.from_numpy(s * np.float32(4.0)))
+    B.idb_routing_entropy_softmax(wt, st, out)
+    # |x| <= 4, so each exponential is within 7 ulp: |1 - log p - H| <= 1 + 4 + log E bounds what it moves H by
+    want = oracle.softmax_entropy(s * np.float32(4.0))
+    assert abs(out.cpu().numpy()[1] - want) <= 7.0 * 2.0 ** -23 * (5.0 + np.log(E)) + 1e-12
