@@ -13,6 +13,7 @@ namespace {
 constexpr int kAuxThreads = 1024;
 constexpr int kAuxWaves = kAuxThreads / 64;
 constexpr int kAuxBatch = 16;  // tile rows a wave has in flight
+static_assert(kAuxMaxBlocks <= 16, "the last workgroup reduces the records inside one row of 16 lanes");
 
 // One workgroup per 64 experts, lane = expert.  Wave w adds the tiles w,
 // w + 16, ... in order (kAuxBatch rows in flight); wave 0 adds the wave sums
@@ -104,21 +105,34 @@ __global__ __launch_bounds__(kAuxThreads) void aux_stats_kernel(const float* __r
         last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
     __syncthreads();
     if (!last) return;
-    if (threadIdx.x == 0) {
-        double L = 0.0;
-        long long S = 0;
+    // one lane per record, so their loads are in flight at once; the sum of f_i
+    // P_i still adds the records in order
+    if (wv == 0) {
+        const int nb = (int)gridDim.x;  // <= kAuxMaxBlocks
+        double fp = 0.0;
+        long long sum = 0;
         int mx = INT32_MIN, mn = INT32_MAX;
-        for (int q = 0; q < (int)gridDim.x; ++q) {
-            L = L + __hip_atomic_load(&partial[q].fp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            S += __hip_atomic_load(&partial[q].sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            mx = max(mx, __hip_atomic_load(&partial[q].max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-            mn = min(mn, __hip_atomic_load(&partial[q].min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        if (lane < nb) {
+            fp = __hip_atomic_load(&partial[lane].fp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            sum = __hip_atomic_load(&partial[lane].sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            mx = __hip_atomic_load(&partial[lane].max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            mn = __hip_atomic_load(&partial[lane].min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        *loss = alpha * L;
-        if (stats) {
-            // MaxVio, MinVio: one fp64 division of an exact integer numerator each
-            stats[0] = (double)((long long)E * mx - S) / (double)S;
-            stats[1] = (double)(S - (long long)E * mn) / (double)S;
+        double L = 0.0;
+        for (int q = 0; q < nb; ++q) L = L + __shfl(fp, q);
+#pragma unroll
+        for (int o = 8; o >= 1; o >>= 1) {
+            sum += __shfl_xor(sum, o);
+            mx = max(mx, __shfl_xor(mx, o));
+            mn = min(mn, __shfl_xor(mn, o));
+        }
+        if (lane == 0) {
+            *loss = alpha * L;
+            if (stats) {
+                // MaxVio, MinVio: one fp64 division of an exact integer numerator each
+                stats[0] = (double)((long long)E * mx - sum) / (double)sum;
+                stats[1] = (double)(sum - (long long)E * mn) / (double)sum;
+            }
         }
     }
 }
