@@ -141,21 +141,32 @@ __device__ __forceinline__ float row_rorf(float x) {
     return __uint_as_float(row_ror<R>(__float_as_uint(x)));
 }
 
+// Number of lanes of the row whose value is strictly greater than this lane's.
+template <int... R>
+__device__ __forceinline__ int row_count_greater(float m, std::integer_sequence<int, R...>) {
+    return ((row_rorf<R + 1>(m) > m ? 1 : 0) + ...);
+}
+
 // For each of this lane's G values: how many of the row's 16 G values are
-// strictly greater.
-template <int R, int G>
-__device__ __forceinline__ void count_greater_step(const float (&m)[G], int (&gt)[G]) {
+// strictly greater.  (A loop that rotates its copy by one lane at a time:
+// unrolled, the compares of all rotations are issued together and spill.)
+template <int G>
+__device__ __forceinline__ void row_count_greater(const float (&m)[G], int (&gt)[G]) {
+    float o[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        const float o = R == 0 ? m[g] : row_rorf<R == 0 ? 1 : R>(m[g]);
-#pragma unroll
-        for (int i = 0; i < G; ++i) gt[i] += o > m[i] ? 1 : 0;
+        o[g] = m[g];
+        gt[g] = 0;
     }
-}
-template <int G, int... R>
-__device__ __forceinline__ void row_count_greater(const float (&m)[G], int (&gt)[G],
-                                                  std::integer_sequence<int, R...>) {
-    (count_greater_step<R, G>(m, gt), ...);
+#pragma unroll 1
+    for (int r = 0; r < 16; ++r) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+#pragma unroll
+            for (int i = 0; i < G; ++i) gt[i] += o[g] > m[i] ? 1 : 0;
+            o[g] = row_rorf<1>(o[g]);
+        }
+    }
 }
 
 __device__ __forceinline__ float row_min(float x) {
@@ -230,13 +241,14 @@ __global__ __launch_bounds__(64 * WAVES) void select_reg_kernel(RouterArgs a, co
                                                                 CtrlArgs ctrl) {
     constexpr int BE = 64 * NV;
     constexpr int TPB = 4 * WAVES;  // tokens per workgroup tile (4 per wave)
-    constexpr int kMaxSel = G == 4 ? kMaxK : 16;  // largest K
+    constexpr int kMaxSel = G == 1 ? 10 : G == 2 ? 16 : kMaxK;  // largest K
     __shared__ __attribute__((aligned(16))) float bias_s[BE];
     __shared__ int hist[BE];
     __shared__ int cnt[TPB];
-    __shared__ unsigned long long lkey[TPB][kRegCap];
-    __shared__ float lsc[TPB][kRegCap];
-    constexpr int SR = kMaxSel + 1;  // odd row stride: the wave's four tokens in distinct banks
+    // (one entry of padding: the four tokens of a wave read distinct banks)
+    __shared__ unsigned long long lkey[TPB][kRegCap + 1];
+    __shared__ float lsc[TPB][kRegCap + 1];
+    constexpr int SR = G == 1 ? 10 : kMaxSel + 1;  // row stride: the wave's four tokens in distinct banks
     __shared__ int sel_i[TPB][SR];
     __shared__ float sel_s[TPB][SR];
     // each lane's first kRegStage marked chunks, copied from its registers
@@ -306,9 +318,8 @@ __global__ __launch_bounds__(64 * WAVES) void select_reg_kernel(RouterArgs a, co
         // groups (-inf) make tau -inf when fewer than K groups hold real
         // columns.
         int gt[G];
-#pragma unroll
-        for (int g = 0; g < G; ++g) gt[g] = 0;
-        row_count_greater<G>(m, gt, std::make_integer_sequence<int, 16>{});
+        if constexpr (G == 1) gt[0] = row_count_greater(m[0], std::make_integer_sequence<int, 15>{});
+        else row_count_greater<G>(m, gt);
         float low = INFINITY;
 #pragma unroll
         for (int g = 0; g < G; ++g) low = fminf(low, gt[g] < K ? m[g] : INFINITY);
@@ -371,21 +382,21 @@ __global__ __launch_bounds__(64 * WAVES) void select_reg_kernel(RouterArgs a, co
         nmax = max(nmax, __builtin_amdgcn_readlane(nl, 32));
         nmax = max(nmax, __builtin_amdgcn_readlane(nl, 48));
         // rank of each listed candidate = the number of list keys above it;
-        // the lanes take the entries in groups of 16
+        // the lanes take the entries in groups of 16.  The lists of the wave's
+        // tokens are filled up to a common length with key 0, below every key,
+        // so the sweep needs no test per key and token.
+        const int nfull = (nmax + 3) & ~3;  // <= kRegCap
+        for (int e = nl + j; e < nfull; e += 16) lkey[slot][e] = 0ull;
+        wave_sync();
         for (int base = 0; base < nmax; base += 16) {
             const int me = base + j;
             const unsigned long long km = me < nl ? lkey[slot][me] : 0ull;
             int rk = 0;
-            int e = 0;
-            for (; e + 4 <= nmax; e += 4) {
+            for (int e = 0; e < nfull; e += 4) {
                 const unsigned long long q0 = lkey[slot][e], q1 = lkey[slot][e + 1];
                 const unsigned long long q2 = lkey[slot][e + 2], q3 = lkey[slot][e + 3];
-                rk += (e < nl && q0 > km) ? 1 : 0;
-                rk += (e + 1 < nl && q1 > km) ? 1 : 0;
-                rk += (e + 2 < nl && q2 > km) ? 1 : 0;
-                rk += (e + 3 < nl && q3 > km) ? 1 : 0;
+                rk += (q0 > km ? 1 : 0) + (q1 > km ? 1 : 0) + (q2 > km ? 1 : 0) + (q3 > km ? 1 : 0);
             }
-            for (; e < nmax; ++e) rk += (e < nl && lkey[slot][e] > km) ? 1 : 0;
             if (me < nl && rk < K) {
                 sel_i[slot][rk] = (int)~(unsigned)km;
                 sel_s[slot][rk] = lsc[slot][me];
@@ -454,7 +465,10 @@ hipError_t launch_select_reg(const RouterArgs& a, const float* scores, const Ctr
         cus = 256;
     if (a.T <= (int64_t)cus * 4 * kRegSmallWaves)
         return launch_select_waves<NV, kRegSmallWaves, G>(a, scores, ctrl, cus, stream);
-    return launch_select_waves<NV, kRegWaves, G>(a, scores, ctrl, cus, stream);
+    // the widest rows with several group maxima need more than the 128 VGPRs of
+    // a 16-wave workgroup
+    constexpr int waves = (NV >= 16 && G >= 2) || (NV >= 12 && G == 4) ? kRegWaves / 2 : kRegWaves;
+    return launch_select_waves<NV, waves, G>(a, scores, ctrl, cus, stream);
 }
 
 template <int G>
