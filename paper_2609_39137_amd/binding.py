@@ -143,9 +143,16 @@ def _check(fn: str, status: int) -> None:
         raise IdbError(fn, status, f"{idb_status_string(status)}: {idb_last_error()}")
 
 
+# The current stream as a raw handle, without a torch.cuda.Stream object for
+# every call (1.5 us of a 13 us call).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int | None:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        if _raw_stream is None or not torch.cuda.is_initialized():
+            return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(torch._C._cuda_getDevice())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
