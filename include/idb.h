@@ -111,7 +111,8 @@ typedef struct idb_controller_state {
  *               summing, Alg. 1).
  *   scores_dump nullable [T][E] fp32 out, 16-byte aligned: the scores s the
  *               selection used (debug / parity; the arithmetic is unchanged).
- *   workspace   device scratch of at least idb_router_workspace_bytes().
+ *   workspace   device scratch of at least idb_router_workspace_bytes(); not
+ *               shared with a call still running on another stream.
  *   variant     0 = automatic tiling; other values force a tiling (see
  *               idb_router_variant_info).  Variants 1-5, 8 and 9 (32x32 MFMA
  *               tiles) give identical outputs; variants 6, 7 and 10 (16x16
@@ -121,7 +122,7 @@ typedef struct idb_controller_state {
  *               The automatic choice depends on T only among tilings of the
  *               same accumulation order: a token's outputs do not depend on
  *               the batch it comes in.
- * With variant 0 a small batch, or one with a large K, may go through a T x E
+ * With variant 0 a small batch, a large K or a row-major W_g may go through a T x E
  * score matrix in the workspace (at most 256 MB, counted in
  * idb_router_workspace_bytes) when the workspace has room for it; with less
  * room, or with a forced variant, the score matrix is never written to memory

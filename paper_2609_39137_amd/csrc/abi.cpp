@@ -529,10 +529,9 @@ idb_status idb_router_step_noalloc(const void* x, const void* W_g, idb_dtype dty
         if (st != IDB_OK) return st;
     }
     void* ws = nullptr;
-    // one-slice tilings need no scratch; the scored path uses it when it fits
-    const bool scratch = need > 0 || (variant == 0 && score_ws_bytes(T, cfg->E) <= have &&
-                                      use_scores(T, cfg->E, K, t, weight_layout == IDB_WEIGHT_ROW_MAJOR));
-    if (scratch) {
+    // one-slice tilings need no scratch and keep to the fused kernel: their
+    // calls may overlap on a device, which sharing the array would forbid
+    if (need > 0) {
         int dev = -1;
         st = hip_result(hipGetDevice(&dev), "current device");
         if (st != IDB_OK) return st;
@@ -547,7 +546,7 @@ idb_status idb_router_step_noalloc(const void* x, const void* W_g, idb_dtype dty
         if (st != IDB_OK) return st;
     }
     return idb_router_step(x, W_g, dtype, weight_layout, T, d, K, cfg, state, expert_idx, gate_w, counts,
-                           accumulate_counts, out_maxvio_minvio, ws, scratch ? have : 0, variant, stream);
+                           accumulate_counts, out_maxvio_minvio, ws, need > 0 ? have : 0, variant, stream);
 }
 
 size_t idb_qb_router_workspace_bytes(int64_t T, int32_t d, int32_t E, int32_t K, idb_dtype dtype,

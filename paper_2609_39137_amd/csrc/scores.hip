@@ -8,7 +8,8 @@
 // (36.9 us at d = 2048, E = 768, two workgroups busy).  Here the tile shrinks
 // with the batch until the launch has about as many workgroups as the chip has
 // CUs, and each wave keeps D chunks of both operands in flight in registers:
-// 5.3 us at T = 32, 11.9 us for T = 777, d = 4096, E = 256 (fused: 92.6 us with
+// 4.9 us at T = 32 (5.4 us with each chunk's operands read from LDS after it is
+// staged), 12.9 us for T = 777, d = 4096, E = 256 row-major (fused: 92.6 us with
 // 128 x 256 tiles), 7.4 us for fp32 T = 4096, d = 256, E = 64 (fused: 29.4 us).
 // The score matrix of such a batch is small enough to stay in L2 and the
 // Infinity Cache between the two launches.
@@ -146,27 +147,53 @@ __global__ __launch_bounds__(WAVES * 64) void score_kernel(RouterArgs a, int NS)
     }
     store_x(0, 0);
     __syncthreads();
-    auto compute = [&](int j, bool prefetch, int cn) {
-        const unsigned char* st = smem + (j & 1) * C::STAGE + boff;
+    auto read_x = [&](int stage, uint4 (&bx)[C::UNITS][TB], int u) {
+        const unsigned char* st = smem + stage * C::STAGE + boff;
 #pragma unroll
-        for (int u = 0; u < C::UNITS; ++u) {
-            uint4 bx[TB];
+        for (int tb = 0; tb < TB; ++tb)
+            bx[u][tb] = *reinterpret_cast<const uint4*>(st + tb * C::MB * kScoreRow + (M32 ? 16 : 64) * u);
+    };
+    auto mfma = [&](int j, const uint4 (&bx)[C::UNITS][TB], int u, bool prefetch, int cn) {
 #pragma unroll
-            for (int tb = 0; tb < TB; ++tb)
-                bx[tb] = *reinterpret_cast<const uint4*>(st + tb * C::MB * kScoreRow + (M32 ? 16 : 64) * u);
+        for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-            for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-                for (int eb = 0; eb < EB; ++eb) {
-                    if constexpr (M32) acc[tb][eb] = mfma_unit<F32>(w[j][eb][u], bx[tb], acc[tb][eb]);
-                    else
-                        acc[tb][eb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            as_bf16x8(w[j][eb][u]), as_bf16x8(bx[tb]), acc[tb][eb], 0, 0, 0);
-                }
-            if (prefetch) {
-#pragma unroll
-                for (int eb = 0; eb < EB; ++eb) w[j][eb][u] = bload16(wres, wvoff + WU * u, wsoff[eb] + cn * WCH);
+            for (int eb = 0; eb < EB; ++eb) {
+                if constexpr (M32) acc[tb][eb] = mfma_unit<F32>(w[j][eb][u], bx[u][tb], acc[tb][eb]);
+                else
+                    acc[tb][eb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(w[j][eb][u]),
+                                                                          as_bf16x8(bx[u][tb]), acc[tb][eb], 0, 0, 0);
             }
+        if (prefetch) {
+#pragma unroll
+            for (int eb = 0; eb < EB; ++eb) w[j][eb][u] = bload16(wres, wvoff + WU * u, wsoff[eb] + cn * WCH);
+        }
+    };
+    // One chunk, and the next one's tokens into the other stage.  A wave alone
+    // needs no barrier (its LDS accesses execute in order): it stages the next
+    // chunk and reads all its operands back before this one's MFMAs, which
+    // cover the round trip; nothing else on its SIMD would.
+    uint4 bq[WAVES == 1 ? 2 : 1][C::UNITS][TB];
+    if constexpr (WAVES == 1) {
+#pragma unroll
+        for (int u = 0; u < C::UNITS; ++u) read_x(0, bq[0], u);
+    }
+    auto step = [&](int j, bool prefetch, int cn) {
+        if constexpr (WAVES == 1) {
+            store_x((j + 1) & 1, (j + 1) % D);
+            wave_sync();
+#pragma unroll
+            for (int u = 0; u < C::UNITS; ++u) read_x((j + 1) & 1, bq[(j + 1) & 1], u);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < C::UNITS; ++u) mfma(j, bq[j & 1], u, prefetch, cn);
+        } else {
+#pragma unroll
+            for (int u = 0; u < C::UNITS; ++u) {
+                read_x(j & 1, bq[0], u);
+                mfma(j, bq[0], u, prefetch, cn);
+            }
+            store_x((j + 1) & 1, (j + 1) % D);
+            __syncthreads();
         }
     };
     int c0 = 0;
@@ -175,18 +202,12 @@ __global__ __launch_bounds__(WAVES * 64) void score_kernel(RouterArgs a, int NS)
         for (int j = 0; j < D; ++j) {
             const int cn = c0 + j + D < last ? c0 + j + D : last;
             load_x(cn, j);
-            compute(j, true, cn);
-            store_x((j + 1) & 1, (j + 1) % D);
-            __syncthreads();
+            step(j, true, cn);
         }
     }
 #pragma unroll
     for (int j = 0; j + 1 < D; ++j) {
-        if (c0 + j < NCH) {
-            compute(j, false, 0);
-            store_x((j + 1) & 1, j + 1);
-            __syncthreads();
-        }
+        if (c0 + j < NCH) step(j, false, 0);
     }
 
     // MFMA output layouts: 16x16 - lane (lr, lg) holds token lr, experts 4 lg + r;
@@ -237,7 +258,7 @@ hipError_t launch_scores(const RouterTiling& t, const RouterArgs& a, hipStream_t
     // launch at d = 2048, E = 768 (16x16; 64 x 192, 64 x 128, 64 x 64, one 16 x 16
     // block per wave): T = 4096 19.3, 22.1, 23.1, -; T = 2048 17.7, 14.8, 16.1, -;
     // T = 1024 -, -, 11.3, -; T = 256 -, -, 7.6 (32 x 64), 7.3; T = 32 -, -, 6.1
-    // (16 x 64), 5.3.  32x32 at d = 1024, E = 1024, T = 5003: 64 x 128 20.4, 64 x 256
+    // (16 x 64), 4.9.  32x32 at d = 1024, E = 1024, T = 5003: 64 x 128 20.4, 64 x 256
     // 24.4, 128 x 256 21.6, 32 x 128 26.1; at d = 4096, E = 256, T = 777: one block
     // per wave 11.9, 32 x 128 15.5, 64 x 128 19.8.
     auto blocks = [&](int bt, int be) { return (a.T + bt - 1) / bt * ((a.E + be - 1) / be); };

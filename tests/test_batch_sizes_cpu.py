@@ -1,0 +1,62 @@
+"""Workspace sizes of the automatic choice over batch sizes (host only): what
+a caller allocates, and that a workspace sized by the fused tiling alone is
+still accepted by the argument checks."""
+import ctypes
+
+import pytest
+
+from paper_2609_39137_amd import binding as B
+
+A16 = ctypes.c_void_p(1 << 12)  # an aligned address that no check dereferences
+
+
+def fused_bytes(T, slices, K):
+    return 3 * ((T * slices * K * 4 + 255) // 256 * 256) + 256 if slices > 1 else 0
+
+
+def scored_bytes(T, E):
+    return (T * E * 4 + 255) // 256 * 256 + 256
+
+
+# (T, d, E, K, dtype, slices, scored, packs): both sides of each line of the
+# choice; `scored` for either weight layout, since the query has none
+@pytest.mark.parametrize("T,d,E,K,dtype,slices,scored,packs", [
+    (32, 2048, 768, 10, 0, 2, True, False),
+    (2560, 2048, 768, 10, 0, 2, True, True),
+    (8192, 2048, 768, 10, 0, 2, True, True),      # row-major only
+    (8193, 2048, 768, 10, 0, 2, False, False),
+    (16384, 2048, 768, 12, 0, 2, False, False),
+    (16384, 2048, 768, 13, 0, 2, True, True),
+    (65536, 2048, 1024, 21, 0, 4, True, True),
+    (65537, 2048, 1024, 21, 0, 4, False, False),  # above 256 MB of scores
+    (777, 4096, 256, 8, 0, 1, True, False),
+    (24577, 4096, 256, 8, 0, 1, False, False),
+    (20480, 512, 128, 8, 0, 1, True, True),
+    (20481, 512, 128, 8, 0, 1, False, False),
+    (32768, 256, 64, 4, 1, 1, True, True),
+    (32769, 256, 64, 4, 1, 1, False, False),
+])
+def test_workspace_covers_the_path_of_either_layout(T, d, E, K, dtype, slices, scored, packs):
+    assert B.idb_router_variant_info(T, d, E, K, dtype, 0)["slices"] == slices
+    want = fused_bytes(T, slices, K)
+    if scored:
+        want = max(want, scored_bytes(T, E) + (E * d * 2 if packs else 0))
+    assert B.idb_router_workspace_bytes(T, d, E, K, dtype, 0) == want
+    # a forced variant keeps the fused tiling's size
+    v = B.idb_router_variant_info(T, d, E, K, dtype, 0)["variant"]
+    assert B.idb_router_workspace_bytes(T, d, E, K, dtype, v) == fused_bytes(T, slices, K)
+
+
+def test_the_fused_workspace_is_the_least_a_call_needs():
+    L = B.lib()
+    T, E, K = 300, 768, 10
+    need = fused_bytes(T, 2, K)
+
+    def call(ws, n):  # a null x is refused after the sizes of the others would be
+        return L.idb_router_merge(T, 128, E, K, 0, A16, A16, None, ws, n, 0, None)
+
+    assert call(A16, need) == B.IDB_ERR_INVALID_ARG  # null counts: refused before any launch
+    assert b"null output" in L.idb_last_error()
+    fwd = [A16, A16, 0, 0, A16, T, 128, E, K, A16, A16, A16, 0, None]
+    assert L.idb_router_forward(*fwd, A16, need - 1, 0, None) == B.IDB_ERR_INVALID_ARG
+    assert b"workspace" in L.idb_last_error()
