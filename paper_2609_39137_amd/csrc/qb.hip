@@ -35,6 +35,7 @@ namespace {
 
 constexpr int kQbThreads = 512;  // the global-memory kernel's workgroup
 constexpr int kQbList = 4096;    // listed keys of a 512-thread workgroup
+constexpr int kFewKeys = 128;    // ranked by counting
 
 // Order-preserving key of a float (after -0 -> +0): a < b iff key(a) < key(b).
 __device__ __forceinline__ unsigned order_key(float d) {
@@ -124,59 +125,9 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Radix select run by one wave over n keys in LDS: the key of ascending rank
-// kleft (1-based), returned to every lane.  h: the wave's 256-bin histogram.
-__device__ unsigned wave_select(const unsigned* vals, unsigned n, unsigned kleft, unsigned* h) {
-    const int lane = threadIdx.x & 63;
-    unsigned prefix = 0u, mask = 0u;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) h[4 * lane + i] = 0u;
-        wave_sync();
-        DigitCounter dc;
-        for (unsigned i = lane; i < n; i += 64) {
-            const unsigned u = vals[i];
-            if ((u & mask) == prefix) dc.add(h, (u >> shift) & 255u);
-        }
-        dc.flush(h);
-        wave_sync();
-        unsigned c[4], tot = 0u;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            c[i] = h[4 * lane + i];
-            tot += c[i];
-        }
-        unsigned incl = tot;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const unsigned up = __shfl_up(incl, o);
-            if (lane >= o) incl += up;
-        }
-        unsigned run = incl - tot, digit = 0u, below = 0u;
-        const bool mine = run < kleft && kleft <= incl;
-        if (mine) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (run < kleft && kleft <= run + c[i]) {
-                    digit = (unsigned)(4 * lane + i);
-                    below = run;
-                }
-                run += c[i];
-            }
-        }
-        const int src = __builtin_ctzll(__ballot(mine));
-        digit = __shfl(digit, src);
-        below = __shfl(below, src);
-        prefix |= digit << shift;
-        mask |= 255u << shift;
-        kleft -= below;
-        wave_sync();  // the histogram is reset by the next pass
-    }
-    return prefix;
-}
-
-// The same selection for n <= 64 * V keys: each lane loads its V keys once
-// and every pass reads registers only.
+// Radix select run by one wave over n <= 64 * V keys in LDS, which each lane
+// loads once: the key of ascending rank kleft (1-based), returned to every
+// lane.  h: the wave's 256-bin histogram.
 // With LOW > 0 the passes stop above bit LOW: the result is the selected
 // key's high bits with the low LOW bits zero, a lower bound of the key.
 template <int V, int LOW = 0>
@@ -297,16 +248,19 @@ struct __attribute__((packed, aligned(4))) f4u {
 // NT threads, R keys per thread in registers (4 <= T <= R * NT): one read of
 // the row.  The wanted key is the r-th largest, r = T - k + 1.
 //   1. A sample of one key per thread, spread over the row, brackets it: the
-//      sample's order statistics 4 standard deviations above and below the
-//      expected rank, from a 16-bit radix select by one wave each (rounded
-//      outwards), give [lo, hi].
+//      sample's order statistics 4 standard deviations above and 6 (and 4
+//      ranks, for the Poisson tail of small ones) below the expected rank, from
+//      a 16-bit radix select by one wave each (rounded outwards), give [lo, hi];
+//      hi is at most the row's largest key.
 //   2. The keys above hi are counted, those in [lo, hi] go to an LDS list
-//      (about T sqrt(r/T) / 4 of them at NT = 1024; 540 at T = 16384, r = 213).
+//      (830 at T = 16384, r = 213; 2800 at T = 50001, r = 1562).
 //   3. The list's histogram over 1024 equal key intervals gives the interval of
-//      the wanted rank; its few keys are ranked by counting.
-// When the bracket misses (the sample does not bind the row), the list
-// overflows, or an interval holds too many keys (ties), a radix select over
-// the list or the registers takes over: the result is exact in every case.
+//      the wanted rank, again inside that interval while it holds many keys
+//      (margins of biases that have drifted together lie close), until its few
+//      keys are ranked by counting or it is a single key.
+// When the bracket misses (the sample does not bind the row) or the list
+// overflows, a radix select over the registers takes over: the result is exact
+// in every case.
 // Bound by reading the row, then by the barriers of the three steps.
 template <int NT, int R>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 ? 6 : 4)))
@@ -324,7 +278,7 @@ void qb_update_reg_kernel(const float* __restrict__ scores_t, const float* __res
     __shared__ unsigned list[LIST];
     __shared__ unsigned sample[NT];  // then the wanted interval's keys
     __shared__ unsigned pick[3];
-    __shared__ unsigned nlist, nabove, nsmall, lo_s, hi_s, result_s;
+    __shared__ unsigned nlist, nabove, nsmall, lo_s, hi_s, max_s, result_s;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int j = blockIdx.x;
@@ -370,6 +324,7 @@ void qb_update_reg_kernel(const float* __restrict__ scores_t, const float* __res
         nsmall = 0u;
         lo_s = 1u;
         hi_s = ~0u;
+        max_s = 0u;
     }
     if ((unsigned)T > LIST / 2) {  // else the whole row goes to the list
         // 1. the bracket; only slots that hold a token of every thread sampled
@@ -382,8 +337,8 @@ void qb_update_reg_kernel(const float* __restrict__ scores_t, const float* __res
         sample[tid] = mine;
         __syncthreads();
         const float share = (float)r_top / (float)T;
-        const float mid = share * (float)ns, dev = 4.0f * sqrtf(mid * (1.0f - share)) + 1.0f;
-        const int hi_rank = (int)(mid - dev), lo_rank = (int)(mid + dev) + 1;  // from the top
+        const float mid = share * (float)ns, dev = sqrtf(mid * (1.0f - share));
+        const int hi_rank = (int)(mid - 4.0f * dev - 1.0f), lo_rank = (int)(mid + 6.0f * dev) + 5;  // from the top
         if (wave == 0 && lo_rank <= ns) {
             const unsigned v = wave_select_reg<NT / 64, 16>(sample, (unsigned)ns, (unsigned)(ns - lo_rank + 1),
                                                             hist[0]);
@@ -399,9 +354,25 @@ void qb_update_reg_kernel(const float* __restrict__ scores_t, const float* __res
     const unsigned lo = lo_s, hi = hi_s;
     // 2. counts above and inside, packed for one scan over the wave; one LDS
     // atomic per wave for its place in the list
-    unsigned c = 0u;
+    unsigned c = 0u, mx = 0u;
 #pragma unroll
-    for (int r = 0; r < R; ++r) c += key[r] > hi ? 0x10000u : key[r] >= lo ? 1u : 0u;
+    for (int r = 0; r < R; ++r) {
+        c += key[r] > hi ? 0x10000u : key[r] >= lo ? 1u : 0u;
+        mx = key[r] > mx ? key[r] : mx;
+    }
+    if (hi == ~0u) {
+        // the row's largest key, one LDS atomic per wave
+        auto up = [](unsigned a, unsigned b) { return a > b ? a : b; };
+        mx = up(mx, (unsigned)row_rot<8>((int)mx));
+        mx = up(mx, (unsigned)row_rot<4>((int)mx));
+        mx = up(mx, (unsigned)row_rot<2>((int)mx));
+        mx = up(mx, (unsigned)row_rot<1>((int)mx));
+        const unsigned wmax = up(up((unsigned)__builtin_amdgcn_readlane((int)mx, 0),
+                                    (unsigned)__builtin_amdgcn_readlane((int)mx, 16)),
+                                 up((unsigned)__builtin_amdgcn_readlane((int)mx, 32),
+                                    (unsigned)__builtin_amdgcn_readlane((int)mx, 48)));
+        if (lane == 0) atomicMax(&max_s, wmax);
+    }
     unsigned incl = c;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -427,50 +398,67 @@ void qb_update_reg_kernel(const float* __restrict__ scores_t, const float* __res
     __syncthreads();
     const unsigned n = nlist, above = nabove;
     if (above < r_top && r_top <= above + n && n <= LIST) {
-        // 3. intervals of 2^sh keys from lo
-        const unsigned want = r_top - above;  // rank from the top of the list
-        const unsigned span = hi - lo;
-        const int sh = span < (unsigned)BINS ? 0 : 22 - __builtin_clz(span);
-        for (unsigned i = tid; i < n; i += NT) atomicAdd(&bins[(list[i] - lo) >> sh], 1u);
-        __syncthreads();
-        if (wave == 0) {
-            // lane l owns the 16 bins below BINS - 16 l
-            const unsigned* own = bins + BINS - 16 * (lane + 1);
-            unsigned cnt[16], tot = 0u;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                cnt[i] = own[i];
-                tot += cnt[i];
-            }
-            unsigned sum = tot;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const unsigned up = __shfl_up(sum, o);
-                if (lane >= o) sum += up;
-            }
-            unsigned run = sum - tot;
-            if (run < want && want <= sum) {
-#pragma unroll
-                for (int i = 15; i >= 0; --i) {
-                    if (run < want && want <= run + cnt[i]) {
-                        pick[0] = (unsigned)(BINS - 16 * (lane + 1) + i);
-                        pick[1] = run;
-                        pick[2] = cnt[i];
-                    }
-                    run += cnt[i];
-                }
-            }
-        }
-        __syncthreads();
-        const unsigned bin = pick[0], m = pick[2], left = want - pick[1];
-        if (m <= (unsigned)NT) {
+        // 3. intervals of 2^sh keys from `from`
+        unsigned want = r_top - above;  // rank from the top of the list
+        unsigned from = lo, m;
+        const unsigned span = (hi == ~0u ? max_s : hi) - lo;
+        int sh = span < (unsigned)BINS ? 0 : 22 - __builtin_clz(span);
+        unsigned width = ~0u;  // keys from `from` on that are looked at, less one
+        for (;;) {
             for (unsigned i = tid; i < n; i += NT) {
                 const unsigned u = list[i];
-                if ((u - lo) >> sh == bin) sample[atomicAdd(&nsmall, 1u)] = u;
+                if (u >= from && u - from <= width) atomicAdd(&bins[(u - from) >> sh], 1u);
+            }
+            __syncthreads();
+            if (wave == 0) {
+                // lane l owns the 16 bins below BINS - 16 l
+                const unsigned* own = bins + BINS - 16 * (lane + 1);
+                unsigned cnt[16], tot = 0u;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    cnt[i] = own[i];
+                    tot += cnt[i];
+                }
+                unsigned sum = tot;
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const unsigned up = __shfl_up(sum, o);
+                    if (lane >= o) sum += up;
+                }
+                unsigned run = sum - tot;
+                if (run < want && want <= sum) {
+#pragma unroll
+                    for (int i = 15; i >= 0; --i) {
+                        if (run < want && want <= run + cnt[i]) {
+                            pick[0] = (unsigned)(BINS - 16 * (lane + 1) + i);
+                            pick[1] = run;
+                            pick[2] = cnt[i];
+                        }
+                        run += cnt[i];
+                    }
+                }
+            }
+            __syncthreads();
+            from += pick[0] << sh;
+            want -= pick[1];
+            m = pick[2];
+            if (sh == 0 || m <= (unsigned)kFewKeys) break;
+            // the next histogram covers this interval alone
+            for (int i = tid; i < BINS; i += NT) bins[i] = 0u;
+            width = (1u << sh) - 1u;
+            sh = sh > 10 ? sh - 10 : 0;
+            __syncthreads();
+        }
+        if (sh == 0) {
+            if (tid == 0) result_s = from;  // one key value per interval
+        } else {
+            for (unsigned i = tid; i < n; i += NT) {
+                const unsigned u = list[i];
+                if (u >= from && (u - from) >> sh == 0u) sample[atomicAdd(&nsmall, 1u)] = u;
             }
             __syncthreads();
             // every thread ranks one key: the wanted one has fewer than
-            // `left` keys above it and at least `left` not below it
+            // `want` keys above it and at least `want` not below it
             if (tid < (int)m) {
                 const unsigned u = sample[tid];
                 unsigned gt = 0u, ge = 0u;
@@ -479,16 +467,10 @@ void qb_update_reg_kernel(const float* __restrict__ scores_t, const float* __res
                     gt += o > u ? 1u : 0u;
                     ge += o >= u ? 1u : 0u;
                 }
-                if (gt < left && left <= ge) result_s = u;  // equal keys write the same value
+                if (gt < want && want <= ge) result_s = u;  // equal keys write the same value
             }
-            __syncthreads();
-        } else {
-            if (wave == 0) {
-                const unsigned u = wave_select(list, n, n - want + 1u, hist[0]);
-                if (lane == 0) result_s = u;
-            }
-            __syncthreads();
         }
+        __syncthreads();
         if (tid == 0) write_bias(bias, j, result_s, rho);
     } else {
         // full radix select over the registers; the empty slots rank lowest

@@ -203,10 +203,12 @@ def qb_case(T, E, kind):
 @pytest.mark.parametrize("T,E,K", [(3, 32, 4), (4, 32, 4), (5, 32, 16), (7, 96, 1), (2048, 32, 8), (2049, 32, 8),
                                    (8191, 32, 16), (8193, 64, 1), (16383, 32, 2), (16385, 32, 8), (32769, 8, 4),
                                    (50001, 32, 1), (65535, 16, 2), (65536, 8, 4), (65537, 8, 2)])
-@pytest.mark.parametrize("kind", ["beta", "sorted", "block", "constant", "levels"])
+@pytest.mark.parametrize("kind", ["beta", "sorted", "block", "constant", "levels", "drifted"])
 def test_qb_update_row_lengths_and_brackets(T, E, K, kind):
     s = qb_case(T, E, kind)
-    b = synth.bias(E, "small", seed=E)
+    # "drifted": Quantile Balancing does not centre its biases, so they wander
+    # off together and the margins lie close in few binades
+    b = synth.bias(E, "small", seed=E) + np.float32(6.0 if kind == "drifted" else 0.0)
     alpha = oracle.qb_alpha(s, b, K)
     for rho in (0.0, 0.5):
         want = oracle.qb_update(s, alpha, K, rho, b.copy())
