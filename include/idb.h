@@ -114,9 +114,9 @@ typedef struct idb_controller_state {
  *   workspace   device scratch of at least idb_router_workspace_bytes(); not
  *               shared with a call still running on another stream.
  *   variant     0 = automatic tiling; other values force a tiling (see
- *               idb_router_variant_info).  Variants 1-5, 8 and 9 (32x32 MFMA
- *               tiles) give identical outputs; variants 6, 7 and 10 (16x16
- *               tiles) accumulate the contraction in another order, so their
+ *               idb_router_variant_info).  Variants 1-5, 8, 9 and 12 (32x32
+ *               MFMA tiles) give identical outputs; variants 6, 7, 10 and 11
+ *               (16x16 tiles) accumulate the contraction in another order, so their
  *               scores can differ in the last fp32 bits.  Given its scores,
  *               every variant's selection, gate weights and counts are exact.
  *               The automatic choice depends on T only among tilings of the

@@ -111,16 +111,17 @@ size_t router_ws_bytes(int64_t T, int32_t E, int32_t K, const idb::RouterTiling&
 //  - fp32: E = 256 T = 8192 45.5 / 53.9, T = 12288 60.5 / 54.5; E = 64 T = 32768
 //    46.5 / 55.0 (d = 512)
 //  - 128-expert tiles: E = 128 T = 16384 32.4 / 38.9, T = 32768 61.7 / 43.9
-//  - K = 8 on 64-token tiles: E = 768 T = 2048 28.6 / 37.3, T = 4096 37.2 / 37.4;
-//    E = 256 T = 3072 24.6 / 28.5, T = 4096 28.8 / 28.8; with d = 512 E = 768 T = 2048
-//    22.3 / 21.2
+//  - K = 8 on 32-token tiles: E = 768 T = 2048 27.2 / 34.1, T = 2560 31.2 / 33.9,
+//    T = 4096 37.2 / 35.0; E = 256 T = 2560 22.6 / 25.5, T = 4096 28.1 / 26.5; with
+//    d = 512, where the selection weighs more, E = 768 T = 1024 17.3 / 18.9, T = 2048
+//    21.4 / 19.3
 //  - K > 12 (the fused lists overflow, the slice merge grows): K = 16 E = 768
 //    T = 50001 245 / 359; E = 512 T = 16384 70.4 / 71.4; E = 1024 T = 16384 142 / 139
 //  - a row-major router matrix, which the fused kernels read at a quarter to
 //    half of the packed rate and the scored path packs first: E = 256 T = 16384
 //    45.6 / 51.1, T = 32768 91.7 / 59.7; E = 768 T = 8192 51.9 / 70.9; E = 1024 T = 8192
 //    66.5 / 64.7
-bool use_scores(int64_t T, int32_t E, int32_t K, const idb::RouterTiling& t, bool row_major) {
+bool use_scores(int64_t T, int32_t d, int32_t E, int32_t K, const idb::RouterTiling& t, bool row_major) {
     const int64_t n = T * E;
     if (n > (int64_t(64) << 20)) return false;  // 256 MB of scores
     if (t.is_f32) return n <= (int64_t(2) << 20);
@@ -130,7 +131,7 @@ bool use_scores(int64_t T, int32_t E, int32_t K, const idb::RouterTiling& t, boo
         return n <= (int64_t(idb::router_slices(t, E) > 1 ? 12 : 3) << 20);
     }
     if (row_major && n <= (int64_t(6) << 20)) return true;
-    return T <= 2560;
+    return T <= (d >= 1024 ? 2560 : 1280);
 }
 
 // From this many tokens on the scored path packs a row-major router matrix
@@ -232,7 +233,7 @@ idb_status prepare_router(const void* x, const void* W_g, idb_dtype dtype, idb_w
     // that was sized for another batch keeps the fused one.
     const size_t scored_need = score_ws_bytes(T, E);
     call->scored = whole && variant == 0 && workspace && workspace_bytes >= scored_need && aligned(workspace, 16) &&
-                   use_scores(T, E, K, call->tiling, layout == IDB_WEIGHT_ROW_MAJOR);
+                   use_scores(T, d, E, K, call->tiling, layout == IDB_WEIGHT_ROW_MAJOR);
     call->pack_to = nullptr;
     if (call->scored) {
         a.scores = reinterpret_cast<float*>(ws);
@@ -293,7 +294,7 @@ size_t idb_router_workspace_bytes(int64_t T, int32_t d, int32_t E, int32_t K, id
     if (resolve_tiling(T, E, dtype, variant, &t) != IDB_OK) return 0;
     const size_t fused = router_ws_bytes(T, E, K, t);
     // room for the path either weight layout may take
-    if (variant != 0 || !(use_scores(T, E, K, t, false) || use_scores(T, E, K, t, true))) return fused;
+    if (variant != 0 || !(use_scores(T, d, E, K, t, false) || use_scores(T, d, E, K, t, true))) return fused;
     const size_t scored = score_ws_bytes(T, E) + (T >= kPackTokens ? weight_bytes(E, d) : 0);
     return scored > fused ? scored : fused;
 }

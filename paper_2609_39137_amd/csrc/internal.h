@@ -67,12 +67,12 @@ struct RouterTiling {
 // Number of known tilings and the i-th one (0-based).
 int router_tiling_count();
 RouterTiling router_tiling(int i);
-// The tiling an automatic choice of t runs T tokens on: t, or its half-size
+// The tiling an automatic choice of t runs T tokens on: t, or a smaller
 // twin for small batches (the same slices, workspace and scores).
 RouterTiling router_tiling_for(const RouterTiling& t, int64_t T, int E);
 
 // 16x16x32 MFMA accumulation order (else 32x32x16, fp32 32x32x2).
-inline bool tiling_is_16(const RouterTiling& t) { return t.id == 6 || t.id == 7 || t.id == 10; }
+inline bool tiling_is_16(const RouterTiling& t) { return t.id == 6 || t.id == 7 || t.id == 10 || t.id == 11; }
 
 struct RouterArgs {
     const void* x;

@@ -739,6 +739,8 @@ hipError_t launch_layout(const RouterTiling& t, const RouterArgs& a, int NS, hip
         case 8: return launch32<false, PACKED, 8, 4, 1>(a, NS, stream, e0, e1);
         case 9: return launch32<false, PACKED, 8, 2, 1>(a, NS, stream, e0, e1);
         case 10: return launch16<PACKED, 8, 4, 3>(a, NS, stream, e0, e1);
+        case 11: return launch16<PACKED, 4, 2, 6>(a, NS, stream, e0, e1);
+        case 12: return launch32<false, PACKED, 4, 1, 2>(a, NS, stream, e0, e1);
         default: return hipErrorInvalidValue;
     }
 }
@@ -760,11 +762,15 @@ const RouterTiling kTilings[] = {
     {8, 0, 8, 128, 32, 3, 0},  // bf16 32x32 tiles: 128 tokens x 256 experts
     {9, 0, 8, 64, 32, 9, 0},   // bf16 32x32 tiles: 64 tokens x 256 experts, two waves per SIMD
     {10, 0, 8, 64, 48, 9, 0},  // bf16 16x16 tiles: 64 tokens x 384 experts, two waves per SIMD
+    {11, 0, 4, 32, 96, 9, 0},  // bf16 16x16 tiles: 32 tokens x 384 experts
+    {12, 0, 4, 32, 64, 9, 0},  // bf16 32x32 tiles: 32 tokens x 256 experts
 };
 
-// The half-size twin (64 instead of 128 tokens per workgroup, the same expert
-// slices and accumulation order) of a tiling, 0 if none.
+// The half- and quarter-size twins (64 and 32 instead of 128 tokens per
+// workgroup, the same expert slices and accumulation order) of a tiling, 0 if
+// none.
 int half_tile(int id) { return id == 6 ? 10 : id == 8 ? 9 : 0; }
+int quarter_tile(int id) { return id == 6 ? 11 : id == 8 ? 12 : 0; }
 
 }  // namespace
 
@@ -777,11 +783,17 @@ RouterTiling router_tiling(int i) { return kTilings[i]; }
 // step at d = 2048, K = 8, 128- against 64-token tiles, us: E = 768, T = 4096:
 // 49.4 -> 37.4, T = 8192 (256 tiles): 50.1 -> 40.9, T = 12288: 54.2 -> 65.7;
 // E = 256, T = 16384 (256 tiles): 45.6 -> 37.2, T = 32768: 53.1 -> 66.5;
-// E = 1024, T = 4096: 57.8 -> 46.0, T = 6144: 58.4 -> 65.4.
+// E = 1024, T = 4096: 57.8 -> 46.0, T = 6144: 58.4 -> 65.4.  32-token tiles (four
+// waves, which read a router row as often as eight) gain less, up to 4096
+// tokens, 64- against 32-token tiles: E = 768, T = 4096: 36.8 -> 35.0; E = 512,
+// T = 4096: 31.2 -> 29.2; E = 384, T = 4096: 33.3 -> 31.4, T = 8192: 34.2 -> 35.4;
+// E = 1024, T = 2048: 42.6 -> 40.8, T = 2560: 42.6 -> 49.8.
 RouterTiling router_tiling_for(const RouterTiling& t, int64_t T, int E) {
     constexpr int64_t kCus = 256;  // MI355X; a constant, so that a shape's tiling needs no HIP call
-    const int half = half_tile(t.id);
-    if (half && (T + 63) / 64 * router_slices(t, E) <= kCus) return kTilings[half - 1];
+    const int half = half_tile(t.id), quarter = quarter_tile(t.id);
+    const int ns = router_slices(t, E);
+    if (quarter && T <= 4096 && (T + 31) / 32 * ns <= kCus) return kTilings[quarter - 1];
+    if (half && (T + 63) / 64 * ns <= kCus) return kTilings[half - 1];
     return t;
 }
 

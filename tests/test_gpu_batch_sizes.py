@@ -1,5 +1,5 @@
-"""The automatic choice over batch sizes: tilings of 64 and 128 tokens per
-workgroup give a token the same bits (scores, selection, gate weights), so its
+"""The automatic choice over batch sizes: tilings of 32, 64 and 128 tokens
+per workgroup give a token the same bits (scores, selection, gate weights), so its
 outputs do not depend on the batch it is routed in.
 
 The comparison is exact: these tilings sum each score over k in the same order
@@ -26,7 +26,7 @@ def equal(got, ref):
 # (variant, the tiling it shares its accumulation order with); one token, the
 # edges of a 64-token tile, several tiles; padded and full expert slices; K up
 # to the largest, where lists overflow and the slice merge ranks 8 lists
-@pytest.mark.parametrize("variant,ref", [(8, 3), (9, 3), (10, 6)])
+@pytest.mark.parametrize("variant,ref", [(8, 3), (9, 3), (10, 6), (11, 6), (12, 3)])
 @pytest.mark.parametrize("T,d,E,K", [(1, 64, 32, 32), (63, 128, 768, 10), (64, 320, 768, 16), (65, 192, 800, 5),
                                      (513, 256, 1024, 32), (200, 64, 256, 1)])
 def test_tilings_of_one_order_agree(variant, ref, T, d, E, K):
@@ -43,17 +43,20 @@ def resolved(T, E):
 
 
 def test_automatic_tiling_by_batch_size():
-    # 64-token tiles while they fit one round of the 256 CUs
+    # 64- and, up to 4096 tokens, 32-token tiles while they fit one round of the 256 CUs
     assert resolved(8192, 768) == 10 and resolved(8193, 768) == 6
     assert resolved(16384, 384) == 10 and resolved(16385, 384) == 6
     assert resolved(16384, 256) == 9 and resolved(16385, 256) == 8
     assert resolved(4096, 1024) == 9 and resolved(4097, 1024) == 8
     assert resolved(1, 128) == 4
+    assert resolved(4096, 768) == 11 and resolved(4097, 768) == 10
+    assert resolved(4096, 256) == 12 and resolved(4097, 256) == 9
+    assert resolved(2048, 1024) == 12 and resolved(2049, 1024) == 9
 
 
-# the last batch on 64-token tiles, the first on 128-token ones: every token
+# the last batch on one tile size and the first on the next: every token
 # they share has the same outputs
-@pytest.mark.parametrize("T,E,K", [(8192, 768, 10), (4096, 1024, 16), (16384, 256, 8)])
+@pytest.mark.parametrize("T,E,K", [(8192, 768, 10), (4096, 768, 10), (4096, 1024, 16), (16384, 256, 8), (4096, 512, 3)])
 def test_a_token_s_outputs_do_not_depend_on_its_batch(T, E, K):
     x, W = synth.normal_router_inputs(T + 1, 64, E, seed=E, w_std=0.05)
     b = synth.bias(E, "small", seed=2)
