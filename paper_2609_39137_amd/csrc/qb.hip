@@ -11,11 +11,11 @@
 // margins' order-preserving 32-bit keys.  Up to 65536 tokens each thread keeps
 // its keys in registers (R <= 64 of them, 512 or 1024 threads; one read of the
 // row at any 4-byte alignment) and a sampled bracket narrows them to a short
-// list (qb_update_reg_kernel).  Measured at T = 16384, E = 768, K = 10: 19.7 us
-// (2.6 TB/s; 22.0 us with a threshold from the per-thread maxima, which also
-// needed a full radix select from r = T K / E > 512 or 1024 on), at T = 50001,
-// E = 256, K = 8: 30.0 us (1.7 TB/s; 145 us recomputing the keys in four radix
-// passes).  Shorter than one piece or longer rows take an MSB-first radix
+// list (qb_update_reg_kernel).  Measured at T = 16384, E = 768, K = 10: 19.4 us
+// (2.6 TB/s), 19.2 us once the biases have drifted off together (21.4 and 23.6
+// us with a threshold from the per-thread maxima, which also needed a full radix
+// select from r = T K / E > 512 or 1024 on); at T = 50001, E = 256, K = 8: 29.2 us
+// (1.8 TB/s; 145 us recomputing the keys in four radix passes).  Shorter than one piece or longer rows take an MSB-first radix
 // select with the keys recomputed from global memory in each of four passes of
 // 8-bit digits.
 //
