@@ -64,6 +64,12 @@ typedef enum idb_weight_layout {
     IDB_WEIGHT_PACKED = 1     /* W_g was written by idb_router_pack_weight (same byte size) */
 } idb_weight_layout;
 
+/* Automatic choices of the router calls' `variant` argument (1 and up force a
+ * tiling).  IDB_ROUTER_AUTO_SCORES is for idb_router_forward and
+ * idb_router_step (and their workspace query): see there. */
+#define IDB_ROUTER_AUTO 0
+#define IDB_ROUTER_AUTO_SCORES (-1)
+
 typedef enum idb_integral_mode {
     IDB_INTEGRAL_ERROR = 0, /* ID Balancing: integral step K_i * e (Eq. rapid-integral)   */
     IDB_INTEGRAL_SIGN = 1   /* DeepSeek loss-free: K_i * sign(e), sign(0) = 0 (Eq. pid-deepseek) */
@@ -111,10 +117,14 @@ typedef struct idb_controller_state {
  *               summing, Alg. 1).
  *   scores_dump nullable [T][E] fp32 out, 16-byte aligned: the scores s the
  *               selection used (debug / parity; the arithmetic is unchanged).
- *   workspace   device scratch of at least idb_router_workspace_bytes(); not
- *               shared with a call still running on another stream.
- *   variant     0 = automatic tiling; other values force a tiling (see
- *               idb_router_variant_info).  Variants 1-5, 8, 9 and 12 (32x32
+ *   workspace   device scratch of at least idb_router_workspace_bytes() for
+ *               this variant; those bytes must not be shared with a call still
+ *               running on another stream.  The call touches no byte past them
+ *               (none at all where they are 0), except with
+ *               IDB_ROUTER_AUTO_SCORES, which owns all workspace_bytes.
+ *   variant     IDB_ROUTER_AUTO = automatic tiling; IDB_ROUTER_AUTO_SCORES =
+ *               the same, or the scored path below; other values force a
+ *               tiling (see idb_router_variant_info).  Variants 1-5, 8, 9 and 12 (32x32
  *               MFMA tiles) give identical outputs; variants 6, 7, 10 and 11
  *               (16x16 tiles) accumulate the contraction in another order, so their
  *               scores can differ in the last fp32 bits.  Given its scores,
@@ -122,13 +132,19 @@ typedef struct idb_controller_state {
  *               The automatic choice depends on T only among tilings of the
  *               same accumulation order: a token's outputs do not depend on
  *               the batch it comes in.
- * With variant 0 a small batch, a large K or a row-major W_g may go through a T x E
- * score matrix in the workspace (at most 256 MB, counted in
- * idb_router_workspace_bytes) when the workspace has room for it; with less
- * room, or with a forced variant, the score matrix is never written to memory
- * unless scores_dump is set.  The outputs are the same bits either way.
+ * Scored path: with IDB_ROUTER_AUTO_SCORES a small batch, a large K or a
+ * row-major W_g may go through a T x E score matrix in the workspace (at most
+ * 256 MB; idb_router_workspace_bytes counts it for whichever weight layout
+ * needs more) when the workspace has room for it, with the same output bits.
+ * With less room it is IDB_ROUTER_AUTO, whose workspace is still the least it
+ * needs.  Otherwise the score matrix is never written to memory unless
+ * scores_dump is set.  idb_router_uses_scores: 1 when a call with these
+ * arguments takes the scored path, else 0 (host only, no HIP call).
  * ------------------------------------------------------------------------- */
 size_t idb_router_workspace_bytes(int64_t T, int32_t d, int32_t E, int32_t K, idb_dtype dtype, int32_t variant);
+
+int32_t idb_router_uses_scores(int64_t T, int32_t d, int32_t E, int32_t K, idb_dtype dtype,
+                               idb_weight_layout weight_layout, size_t workspace_bytes, int32_t variant);
 
 idb_status idb_router_forward(const void* x, const void* W_g, idb_dtype dtype, idb_weight_layout weight_layout,
                               const float* bias, int64_t T,
@@ -136,9 +152,9 @@ idb_status idb_router_forward(const void* x, const void* W_g, idb_dtype dtype, i
                               int32_t* counts, int32_t accumulate_counts, float* scores_dump, void* workspace,
                               size_t workspace_bytes, int32_t variant, hipStream_t stream);
 
-/* The two launches idb_router_forward makes, exposed so a caller can time or
- * overlap them separately.  Same arguments; calling score_select then merge
- * on one stream is exactly idb_router_forward.
+/* The two launches idb_router_forward makes with a tiling (variant 0 and up),
+ * exposed so a caller can time or overlap them separately.  Same arguments;
+ * calling score_select then merge on one stream is exactly idb_router_forward.
  *   score_select: gate contraction, sigmoid, biased Top-K per expert slice
  *                 (and, when the tiling covers all experts in one slice, the
  *                 final outputs); zeroes counts unless accumulating.
@@ -244,7 +260,8 @@ idb_status idb_controller_step(const int32_t* counts, const idb_controller_cfg* 
  * as for those calls, with the same workspace size.  With accumulate_counts
  * the update uses the accumulated counts (the last microbatch of an
  * iteration).  Two launches for multi-slice tilings: the fused router kernel,
- * then the slice merge, whose last workgroup to finish applies the update.
+ * then the slice merge, whose last workgroup to finish applies the update (the
+ * scored path: the scores, then the selection, whose last workgroup does).
  * The workspace must not be shared with a call still running on another
  * stream.
  * ------------------------------------------------------------------------- */
@@ -281,7 +298,8 @@ idb_status idb_router_merge_step(int64_t T, int32_t d, int32_t K, idb_dtype dtyp
  * - Size limit: the tiling's workspace (idb_router_workspace_bytes) must fit
  *   in IDB_NOALLOC_SCRATCH_BYTES, e.g. T <= 65536 at E = 768, K <= 10 on the
  *   default tiling; larger shapes return IDB_ERR_UNSUPPORTED and enqueue
- *   nothing.  One-slice tilings need no scratch.
+ *   nothing.  One-slice tilings need no scratch and never touch the array;
+ *   several slices with variant 0 may take the scored path in it.
  * - The stream must belong to the calling thread's current device (else
  *   IDB_ERR_INVALID_ARG).  The first call on a device looks up the array's
  *   address there (hipGetSymbolAddress) and keeps it.

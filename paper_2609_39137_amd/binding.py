@@ -26,6 +26,8 @@ IDB_DTYPE_BF16 = 0
 IDB_DTYPE_F32 = 1
 IDB_WEIGHT_ROW_MAJOR = 0
 IDB_WEIGHT_PACKED = 1
+IDB_ROUTER_AUTO = 0
+IDB_ROUTER_AUTO_SCORES = -1
 IDB_INTEGRAL_ERROR = 0
 IDB_INTEGRAL_SIGN = 1
 
@@ -37,6 +39,7 @@ EXPORTED = (
     "idb_qb_update", "idb_controller_update_layers", "idb_routing_entropy_workspace_bytes", "idb_routing_entropy",
     "idb_aux_router_workspace_bytes", "idb_aux_router_forward", "idb_router_merge_step",
     "idb_router_step_noalloc", "idb_routing_entropy_softmax", "idb_router_score_select_timed",
+    "idb_router_uses_scores",
 )
 
 
@@ -71,6 +74,8 @@ def lib() -> ctypes.CDLL:
     router_args = [P, P, i32, i32, P, i64, i32, i32, i32, P, P, P, i32, P, P, sz, i32, P]
     L.idb_router_workspace_bytes.argtypes = [i64, i32, i32, i32, i32, i32]
     L.idb_router_workspace_bytes.restype = sz
+    L.idb_router_uses_scores.argtypes = [i64, i32, i32, i32, i32, i32, sz, i32]
+    L.idb_router_uses_scores.restype = i32
     for name in ("idb_router_forward", "idb_router_score_select"):
         getattr(L, name).argtypes = router_args
         getattr(L, name).restype = ctypes.c_int
@@ -177,6 +182,13 @@ def _dtype_code(t: torch.Tensor) -> int:
 
 def idb_router_workspace_bytes(T: int, d: int, E: int, K: int, dtype: int, variant: int = 0) -> int:
     return int(lib().idb_router_workspace_bytes(T, d, E, K, dtype, variant))
+
+
+def idb_router_uses_scores(T: int, d: int, E: int, K: int, dtype: int, weight_layout: int, workspace_bytes: int,
+                           variant: int = IDB_ROUTER_AUTO_SCORES) -> bool:
+    """Whether ``idb_router_forward`` / ``idb_router_step`` with these arguments go through the T x E scores in the
+    workspace (see ``IDB_ROUTER_AUTO_SCORES`` in the header)."""
+    return bool(lib().idb_router_uses_scores(T, d, E, K, dtype, weight_layout, workspace_bytes, variant))
 
 
 def idb_router_variant_info(T: int, d: int, E: int, K: int, dtype: int, variant: int = 0) -> dict:

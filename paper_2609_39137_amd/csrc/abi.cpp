@@ -171,9 +171,14 @@ idb_status prepare_router(const void* x, const void* W_g, idb_dtype dtype, idb_w
                           int32_t accumulate_counts, float* scores_dump, void* workspace, size_t workspace_bytes,
                           int32_t variant, bool need_inputs, RouterCall* call, bool qb = false,
                           bool aux = false, bool whole = false) {
-    // whole: the call makes all of the step's launches itself (the split calls
-    // keep the fused tiling, whose slices their callers can query), so the
-    // automatic choice may take the scored path
+    // whole: the call makes all of the step's launches itself, so it accepts
+    // IDB_ROUTER_AUTO_SCORES (the split calls refuse it: their second launch
+    // could not tell which path the first one took).  Only that choice uses
+    // more of the workspace than the tiling's own part: a caller of variant 0
+    // may keep other data there, or share it between streams where the tiling
+    // needs none.
+    const bool own_workspace = whole && variant == IDB_ROUTER_AUTO_SCORES;
+    if (own_workspace) variant = IDB_ROUTER_AUTO;
     // Quantile Balancing keeps K + 1 candidates per token (the (K+1)-th is the cutoff)
     const int32_t KL = qb ? K + 1 : K;
     idb_status st = check_router_shape(T, d, E, KL, dtype);
@@ -232,7 +237,7 @@ idb_status prepare_router(const void* x, const void* W_g, idb_dtype dtype, idb_w
     // The scored path may need more scratch than the fused tiling: a workspace
     // that was sized for another batch keeps the fused one.
     const size_t scored_need = score_ws_bytes(T, E);
-    call->scored = whole && variant == 0 && workspace && workspace_bytes >= scored_need && aligned(workspace, 16) &&
+    call->scored = own_workspace && workspace && aligned(workspace, 16) && workspace_bytes >= scored_need &&
                    use_scores(T, d, E, K, call->tiling, layout == IDB_WEIGHT_ROW_MAJOR);
     call->pack_to = nullptr;
     if (call->scored) {
@@ -290,13 +295,23 @@ extern "C" {
 
 size_t idb_router_workspace_bytes(int64_t T, int32_t d, int32_t E, int32_t K, idb_dtype dtype, int32_t variant) {
     if (check_router_shape(T, d, E, K, dtype) != IDB_OK) return 0;
+    const bool own_workspace = variant == IDB_ROUTER_AUTO_SCORES;
     idb::RouterTiling t;
-    if (resolve_tiling(T, E, dtype, variant, &t) != IDB_OK) return 0;
+    if (resolve_tiling(T, E, dtype, own_workspace ? IDB_ROUTER_AUTO : variant, &t) != IDB_OK) return 0;
     const size_t fused = router_ws_bytes(T, E, K, t);
     // room for the path either weight layout may take
-    if (variant != 0 || !(use_scores(T, d, E, K, t, false) || use_scores(T, d, E, K, t, true))) return fused;
+    if (!own_workspace || !(use_scores(T, d, E, K, t, false) || use_scores(T, d, E, K, t, true))) return fused;
     const size_t scored = score_ws_bytes(T, E) + (T >= kPackTokens ? weight_bytes(E, d) : 0);
     return scored > fused ? scored : fused;
+}
+
+int32_t idb_router_uses_scores(int64_t T, int32_t d, int32_t E, int32_t K, idb_dtype dtype,
+                               idb_weight_layout weight_layout, size_t workspace_bytes, int32_t variant) {
+    idb::RouterTiling t;
+    if (variant != IDB_ROUTER_AUTO_SCORES || check_router_shape(T, d, E, K, dtype) != IDB_OK ||
+        resolve_tiling(T, E, dtype, IDB_ROUTER_AUTO, &t) != IDB_OK)
+        return 0;
+    return workspace_bytes >= score_ws_bytes(T, E) && use_scores(T, d, E, K, t, weight_layout == IDB_WEIGHT_ROW_MAJOR);
 }
 
 idb_status idb_router_variant_info(int64_t T, int32_t d, int32_t E, int32_t K, idb_dtype dtype, int32_t variant,
@@ -531,8 +546,10 @@ idb_status idb_router_step_noalloc(const void* x, const void* W_g, idb_dtype dty
     }
     void* ws = nullptr;
     // one-slice tilings need no scratch and keep to the fused kernel: their
-    // calls may overlap on a device, which sharing the array would forbid
+    // calls may overlap on a device, which sharing the array would forbid; the
+    // others have the whole array to themselves
     if (need > 0) {
+        if (variant == IDB_ROUTER_AUTO) variant = IDB_ROUTER_AUTO_SCORES;
         int dev = -1;
         st = hip_result(hipGetDevice(&dev), "current device");
         if (st != IDB_OK) return st;

@@ -5,6 +5,12 @@ counts, load statistics), the router workspace and the controller state of one
 MoE layer, all as device tensors, and issues the ABI calls of one iteration of
 Alg. 1: route the batch with the current bias, update the bias from the
 counts, and compute MaxVio/MinVio.
+
+The workspace is the step's own, so with ``variant`` 0 :meth:`RouterStep.route`
+and :meth:`RouterStep.step` pass ``IDB_ROUTER_AUTO_SCORES`` and may go through a
+T x E score matrix in it (:meth:`RouterStep.uses_scores`); it is sized for a
+row-major and for a packed router matrix, whichever needs more.  ``info``
+describes the fused tiling, which the other calls always run.
 """
 from __future__ import annotations
 
@@ -25,7 +31,8 @@ class RouterStep:
         self.w = torch.empty((T, K), dtype=torch.float32, device=device)
         self.counts = torch.zeros(E, dtype=torch.int32, device=device)
         self.stats = torch.zeros(2, dtype=torch.float64, device=device)
-        nbytes = B.idb_router_workspace_bytes(T, d, E, K, code, variant)
+        self._whole_variant = B.IDB_ROUTER_AUTO_SCORES if variant == B.IDB_ROUTER_AUTO else variant
+        nbytes = B.idb_router_workspace_bytes(T, d, E, K, code, self._whole_variant)
         self.workspace = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=device)
         self.info = B.idb_router_variant_info(T, d, E, K, code, variant)
         self.W_packed = None
@@ -45,11 +52,18 @@ class RouterStep:
             return self.W_packed, B.IDB_WEIGHT_PACKED
         return W, B.IDB_WEIGHT_ROW_MAJOR
 
+    def uses_scores(self, packed: bool) -> bool:
+        """Whether :meth:`route` and :meth:`step` go through the score matrix, with the packed router matrix or a
+        row-major one."""
+        return B.idb_router_uses_scores(self.T, self.d, self.E, self.K, self.dtype_code,
+                                        B.IDB_WEIGHT_PACKED if packed else B.IDB_WEIGHT_ROW_MAJOR,
+                                        self.workspace.numel(), self._whole_variant)
+
     def route(self, x, W=None, accumulate: bool = False, scores_dump=None, stream=None):
         """Route with row-major ``W``, or with the packed copy from :meth:`pack` when ``W`` is None."""
         Wt, layout = self._weights(W)
         B.idb_router_forward(x, Wt, self.state.bias, self.K, self.idx, self.w, self.counts, accumulate, scores_dump,
-                             self.workspace, self.variant, stream, layout)
+                             self.workspace, self._whole_variant, stream, layout)
 
     def score_select(self, x, W=None, accumulate: bool = False, scores_dump=None, stream=None, events=None):
         """The router's first launch; ``events`` = (start, stop) ``torch.cuda.Event`` pair that then takes the
@@ -82,7 +96,7 @@ class RouterStep:
         the slice merge's last workgroup when the tiling has several slices)."""
         Wt, layout = self._weights(W)
         B.idb_router_step(x, Wt, self.K, self.cfg, self.state, self.idx, self.w, self.counts, accumulate,
-                          self.stats, self.workspace, self.variant, stream, layout)
+                          self.stats, self.workspace, self._whole_variant, stream, layout)
 
     def merge_step(self, stream=None):
         """The second launch of :meth:`step` after :meth:`score_select` (same bias, same outputs): slice merge,

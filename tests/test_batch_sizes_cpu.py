@@ -1,6 +1,6 @@
-"""Workspace sizes of the automatic choice over batch sizes (host only): what
-a caller allocates, and that a workspace sized by the fused tiling alone is
-still accepted by the argument checks."""
+"""Workspace sizes of the automatic choices over batch sizes (host only): what
+a caller allocates, that the plain choice asks for the fused tiling's part alone
+(and so keeps to it), and which calls take the scored path."""
 import ctypes
 
 import pytest
@@ -38,13 +38,33 @@ def scored_bytes(T, E):
 ])
 def test_workspace_covers_the_path_of_either_layout(T, d, E, K, dtype, slices, scored, packs):
     assert B.idb_router_variant_info(T, d, E, K, dtype, 0)["slices"] == slices
-    want = fused_bytes(T, slices, K)
-    if scored:
-        want = max(want, scored_bytes(T, E) + (E * d * 2 if packs else 0))
-    assert B.idb_router_workspace_bytes(T, d, E, K, dtype, 0) == want
-    # a forced variant keeps the fused tiling's size
+    fused = fused_bytes(T, slices, K)
+    want = max(fused, scored_bytes(T, E) + (E * d * 2 if packs else 0)) if scored else fused
+    assert B.idb_router_workspace_bytes(T, d, E, K, dtype, B.IDB_ROUTER_AUTO_SCORES) == want
+    # the plain automatic choice and a forced variant use the fused tiling's part only
     v = B.idb_router_variant_info(T, d, E, K, dtype, 0)["variant"]
-    assert B.idb_router_workspace_bytes(T, d, E, K, dtype, v) == fused_bytes(T, slices, K)
+    assert B.idb_router_workspace_bytes(T, d, E, K, dtype, 0) == fused
+    assert B.idb_router_workspace_bytes(T, d, E, K, dtype, v) == fused
+    # the path: with that workspace some layout takes it; with one too small
+    # for the scores, or without the choice that owns the workspace, none does
+    layouts = (B.IDB_WEIGHT_ROW_MAJOR, B.IDB_WEIGHT_PACKED)
+    assert any(B.idb_router_uses_scores(T, d, E, K, dtype, w, want) for w in layouts) == scored
+    for w in layouts:
+        assert not B.idb_router_uses_scores(T, d, E, K, dtype, w, scored_bytes(T, E) - 1)
+        assert not B.idb_router_uses_scores(T, d, E, K, dtype, w, 1 << 40, 0)
+        assert not B.idb_router_uses_scores(T, d, E, K, dtype, w, 1 << 40, v)
+
+
+def test_only_whole_router_calls_accept_the_workspace_owning_choice():
+    L, v = B.lib(), B.IDB_ROUTER_AUTO_SCORES
+    args = [A16, A16, 0, 0, A16, 300, 128, 768, 10, A16, A16, A16, 0, None, A16, 1 << 30, v, None]
+    assert L.idb_router_score_select(*args) == B.IDB_ERR_INVALID_ARG
+    assert L.idb_router_merge(300, 128, 768, 10, 0, A16, A16, A16, A16, 1 << 30, v, None) == B.IDB_ERR_INVALID_ARG
+    assert B.idb_qb_router_workspace_bytes(300, 128, 768, 10, 0, v) == 0
+    assert B.idb_aux_router_workspace_bytes(300, 128, 768, 10, 0, v) == 0
+    args[14], args[15] = A16, fused_bytes(300, 2, 10) - 1  # as variant 0: the fused part is the least
+    assert L.idb_router_forward(*args) == B.IDB_ERR_INVALID_ARG
+    assert b"workspace" in L.idb_last_error()
 
 
 def test_the_fused_workspace_is_the_least_a_call_needs():

@@ -110,17 +110,49 @@ def test_scored_path_equals_the_fused_tiling(T, d, E, K, dtype, packed, ties):
         np.testing.assert_array_equal(a.view(np.uint32), g.view(np.uint32))
 
 
+# one-slice tilings (no workspace of their own) and several slices, both types
+@pytest.mark.parametrize("T,d,E,K,dtype", [(300, 128, 256, 8, "bf16"), (1100, 64, 64, 32, "bf16"), (100, 64, 64, 4, "f32"),
+                                           (300, 128, 768, 10, "bf16"), (2000, 64, 1024, 24, "bf16")])
+def test_variant_0_touches_only_its_part_of_the_workspace(T, d, E, K, dtype):
+    # the rest of a pooled scratch may belong to calls on other streams; the
+    # choice that owns it all gives the same bits
+    x, W = synth.normal_router_inputs(T, d, E, seed=T, dtype=dtype, w_std=0.05)
+    code = B.IDB_DTYPE_BF16 if dtype == "bf16" else B.IDB_DTYPE_F32
+    bias = torch.from_numpy(synth.bias(E, "small", seed=1)).to(DEV)
+    own = B.idb_router_workspace_bytes(T, d, E, K, code, 0)
+    size = max(own, T * E * 4 + E * d * 4) + 4096
+    outs = []
+    for variant in (0, B.IDB_ROUTER_AUTO_SCORES):
+        pool = torch.full((size,), 0x5A, dtype=torch.uint8, device=DEV)
+        st = B.ControllerState(E, DEV)
+        st.bias.copy_(bias)
+        idx = torch.empty((T, K), dtype=torch.int32, device=DEV)
+        w = torch.empty((T, K), dtype=torch.float32, device=DEV)
+        c = torch.empty(E, dtype=torch.int32, device=DEV)
+        stats = torch.empty(2, dtype=torch.float64, device=DEV)
+        got = []
+        B.idb_router_forward(to_dev(x), to_dev(W), bias, K, idx, w, c, workspace=pool, variant=variant)
+        got += [t.cpu().numpy() for t in (idx, w, c)]
+        B.idb_router_step(to_dev(x), to_dev(W), K, B.ControllerCfg(E), st, idx, w, c, False, stats, pool, variant)
+        got += [t.cpu().numpy() for t in (idx, w, c, st.bias, st.e_prev, st.step, stats)]
+        outs.append(got)
+        untouched = bool((pool[own:] == 0x5A).all())
+        scored = B.idb_router_uses_scores(T, d, E, K, code, B.IDB_WEIGHT_ROW_MAJOR, size, variant)
+        assert scored == (variant != 0) and untouched == (variant == 0)
+    equal(*outs)
+
+
 def test_a_workspace_sized_for_the_fused_tiling_keeps_it():
     # a caller that sized its workspace by the fused tiling (or passes none to
     # a one-slice tiling) is served as before, with the same outputs
     for T, E, K, ws_bytes in ((300, 768, 10, 3 * (300 * 2 * 10 * 4 + 255) // 256 * 256 + 1024), (300, 256, 8, 0)):
         x, W = synth.normal_router_inputs(T, 128, E, seed=T, w_std=0.05)
         want = run_router(x, W, synth.bias(E, "small", seed=1), K, dump=False)
-        assert B.idb_router_workspace_bytes(T, 128, E, K, B.IDB_DTYPE_BF16, 0) > ws_bytes
+        assert B.idb_router_workspace_bytes(T, 128, E, K, B.IDB_DTYPE_BF16, B.IDB_ROUTER_AUTO_SCORES) > ws_bytes
         idx = torch.empty((T, K), dtype=torch.int32, device=DEV)
         w = torch.empty((T, K), dtype=torch.float32, device=DEV)
         c = torch.empty(E, dtype=torch.int32, device=DEV)
         ws = torch.empty(ws_bytes, dtype=torch.uint8, device=DEV) if ws_bytes else None
         B.idb_router_forward(to_dev(x), to_dev(W), torch.from_numpy(synth.bias(E, "small", seed=1)).to(DEV), K, idx, w,
-                             c, workspace=ws)
+                             c, workspace=ws, variant=B.IDB_ROUTER_AUTO_SCORES)
         equal([idx.cpu().numpy(), w.cpu().numpy(), c.cpu().numpy()], want[:3])
