@@ -141,6 +141,8 @@ bool use_scores(int64_t T, int32_t d, int32_t E, int32_t K, const idb::RouterTil
 // unpacked, 8.4 packed).
 constexpr int64_t kPackTokens = 1024;
 
+bool packs_first(int64_t T, idb_dtype dtype) { return T >= kPackTokens && dtype == IDB_DTYPE_BF16; }
+
 size_t weight_bytes(int32_t E, int32_t d) { return (size_t)E * d * 2; }
 
 // Its workspace: the scores [T][E], the ticket, then (when there is room) the
@@ -247,7 +249,7 @@ idb_status prepare_router(const void* x, const void* W_g, idb_dtype dtype, idb_w
         a.zero_counts = accumulate_counts ? 0 : 1;
         a.cand_v = a.cand_s = nullptr;
         a.cand_i = nullptr;
-        if (layout == IDB_WEIGHT_ROW_MAJOR && T >= kPackTokens && dtype == IDB_DTYPE_BF16 &&
+        if (layout == IDB_WEIGHT_ROW_MAJOR && packs_first(T, dtype) &&
             workspace_bytes - scored_need >= weight_bytes(E, d))
             call->pack_to = ws + scored_need;
     }
@@ -301,7 +303,7 @@ size_t idb_router_workspace_bytes(int64_t T, int32_t d, int32_t E, int32_t K, id
     const size_t fused = router_ws_bytes(T, E, K, t);
     // room for the path either weight layout may take
     if (!own_workspace || !(use_scores(T, d, E, K, t, false) || use_scores(T, d, E, K, t, true))) return fused;
-    const size_t scored = score_ws_bytes(T, E) + (T >= kPackTokens ? weight_bytes(E, d) : 0);
+    const size_t scored = score_ws_bytes(T, E) + (packs_first(T, dtype) ? weight_bytes(E, d) : 0);
     return scored > fused ? scored : fused;
 }
 

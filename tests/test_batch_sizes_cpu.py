@@ -33,7 +33,7 @@ def scored_bytes(T, E):
     (24577, 4096, 256, 8, 0, 1, False, False),
     (20480, 512, 128, 8, 0, 1, True, True),
     (20481, 512, 128, 8, 0, 1, False, False),
-    (32768, 256, 64, 4, 1, 1, True, True),
+    (32768, 256, 64, 4, 1, 1, True, False),       # fp32 is never packed on the way
     (32769, 256, 64, 4, 1, 1, False, False),
 ])
 def test_workspace_covers_the_path_of_either_layout(T, d, E, K, dtype, slices, scored, packs):
