@@ -69,6 +69,11 @@ __device__ __forceinline__ double row_rot(double x) {
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
+// Four floats at any 4-byte aligned address (rows of odd length).
+struct __attribute__((packed, aligned(4))) f4u {
+    float v[4];
+};
+
 // Raw buffer resource over [base, base + bytes) (bytes < 2^32) and a 16-byte
 // load at per-lane offset voff plus scalar offset soff.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, int64_t bytes) {

@@ -39,11 +39,6 @@ __device__ inline double block_sum_fixed(double v, double* red) {
     return t;
 }
 
-// Four floats at any 4-byte aligned address (rows of odd length).
-struct __attribute__((packed, aligned(4))) f4u {
-    float v[4];
-};
-
 // A row's values of this lane: columns 4 (lane + 64 p) .. + 3 for p < NP
 // (256 NP >= E); `pad` past the row.
 template <int NP>

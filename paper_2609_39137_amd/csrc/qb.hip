@@ -117,20 +117,11 @@ __device__ __forceinline__ void write_bias(float* bias, int j, unsigned key, flo
     }
 }
 
-// Orders the LDS accesses of one wave's lanes (a code-motion barrier; a wave's
-// LDS operations execute in order).
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Radix select run by one wave over n <= 64 * V keys in LDS, which each lane
-// loads once: the key of ascending rank kleft (1-based), returned to every
-// lane.  h: the wave's 256-bin histogram.
-// With LOW > 0 the passes stop above bit LOW: the result is the selected
-// key's high bits with the low LOW bits zero, a lower bound of the key.
-template <int V, int LOW = 0>
+// loads once: the high bits of the key of ascending rank kleft (1-based), down
+// to bit LOW and with zeros below it, a lower bound of that key, returned to
+// every lane.  h: the wave's 256-bin histogram.
+template <int V, int LOW>
 __device__ unsigned wave_select_reg(const unsigned* vals, unsigned n, unsigned kleft, unsigned* h) {
     const int lane = threadIdx.x & 63;
     unsigned v[V];
@@ -239,11 +230,6 @@ __device__ __forceinline__ void qb_stats_load(const int32_t* __restrict__ counts
         n[q] = i < E ? counts[i] : 0;
     }
 }
-
-// Four floats at any 4-byte aligned address (rows of odd length).
-struct __attribute__((packed, aligned(4))) f4u {
-    float v[4];
-};
 
 // NT threads, R keys per thread in registers (4 <= T <= R * NT): one read of
 // the row.  The wanted key is the r-th largest, r = T - k + 1.

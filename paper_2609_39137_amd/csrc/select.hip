@@ -16,7 +16,7 @@
 //    (16 at K = 10, G = 1; 22 at K = 16, G = 2; 44 at K = 32, G = 4), and with
 //    G = 1 every list overflows from K = 16 on.  It also ends the router's
 //    scored path, where its last workgroup applies the controller update.
-//  * select_kernel (every other case): a workgroup of 512 threads walks tiles
+//  * select_kernel (other row lengths and alignments): a workgroup of 512 threads walks tiles
 //    of 32 tokens (grid-stride, one workgroup per CU: the score rows of a tile
 //    take most of the LDS).  A tile's scores go from registers into the LDS
 //    score rows of the selection epilogue (epilogue.h, one slice of BE >= E
@@ -48,14 +48,13 @@ __global__ void fill_i32_kernel(int32_t* p, int32_t value, int64_t n) {
         p[i] = value;
 }
 
-// BE: the slice width (a multiple of 256 >= E); VEC: E % 4 == 0 and 16-byte
-// aligned scores, so a tile row is read as float4 pieces.
-template <int BE, bool VEC>
+// BE: the slice width (a multiple of 256 >= E).
+template <int BE>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(RouterArgs a, const float* __restrict__ scores) {
     using EC = EpiCfg<kSelThreads, kSelTile, BE, 0, kSelScoreLds>;
     static_assert(EC::NPASS == 1, "one pass per tile");
     __shared__ __attribute__((aligned(16))) unsigned char smem[EC::LDS];
-    constexpr int PIECES = kSelTile * BE / 4;      // float4 pieces of a tile
+    constexpr int PIECES = kSelTile * BE / 4;      // pieces of four scores of a tile
     constexpr int PER = PIECES / kSelThreads;      // per thread
     static_assert(PER * kSelThreads == PIECES, "tile pieces split evenly");
     const int tid = threadIdx.x;
@@ -77,14 +76,10 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(RouterArgs a, const
             float4 f = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
             if (t < T) {
                 const float* src = scores + t * (int64_t)E + c4;
-                if (VEC) {
-                    if (c4 < E) f = *reinterpret_cast<const float4*>(src);
-                } else {
-                    if (c4 + 0 < E) f.x = src[0];
-                    if (c4 + 1 < E) f.y = src[1];
-                    if (c4 + 2 < E) f.z = src[2];
-                    if (c4 + 3 < E) f.w = src[3];
-                }
+                if (c4 + 0 < E) f.x = src[0];
+                if (c4 + 1 < E) f.y = src[1];
+                if (c4 + 2 < E) f.z = src[2];
+                if (c4 + 3 < E) f.w = src[3];
             }
             r[i] = f;
         }
@@ -117,11 +112,7 @@ hipError_t launch_select_be(const RouterArgs& a, const float* scores, hipStream_
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         cus = 256;
     const int grid = (int)(ntiles < cus ? ntiles : cus);
-    const bool vec = (a.E % 4 == 0) && ((reinterpret_cast<uintptr_t>(scores) & 15) == 0);
-    if (vec)
-        hipLaunchKernelGGL((select_kernel<BE, true>), dim3(grid), dim3(kSelThreads), 0, stream, a, scores);
-    else
-        hipLaunchKernelGGL((select_kernel<BE, false>), dim3(grid), dim3(kSelThreads), 0, stream, a, scores);
+    hipLaunchKernelGGL((select_kernel<BE>), dim3(grid), dim3(kSelThreads), 0, stream, a, scores);
     return hipGetLastError();
 }
 
