@@ -450,12 +450,20 @@ __global__ __launch_bounds__(WAVES * 64) void router16_kernel(RouterArgs a, int 
     select_epilogue<EC, SM>(a, NS, slice, tok0, smem, breg, store_pass);
 }
 
-// How many of a slice's n rank-ordered (descending) keys are above k, by
-// binary search: the lists come sorted out of the epilogue.  Against a scan of
-// the list, whole steps at K = 16, T = 4096, d = 2048 (64 candidates per token
-// at E = 1024): 95.6 -> 88.5 us together with 8-wave tiles.
+// How many of a slice's n rank-ordered (descending) keys are above k.  The
+// lists come sorted out of the epilogue, so a binary search finds it, but its
+// probes depend on each other and, with lists of 8 or 16 keys, meet in a few
+// LDS banks; a scan of a short list reads 8 keys at once.  Whole steps, scan
+// against search, us: n = 8: E = 800 T = 8192 d = 64 61.3 / 73.0, fp32 E = 1024 T =
+// 2560 d = 32 51.2 / 66.7; n = 10: search 1.01 to 1.03 times the scan; n = 16: 1.01
+// to 1.10; n = 12 and 14: 0.96 and 0.89 on average over 4 slices; n > 16: 0.99.
 __device__ __forceinline__ int count_above(const unsigned long long* list, int n, unsigned long long k) {
     int lo = 0;
+    if (n <= 10 || n == 16) {  // uniform: the list length of the launch
+#pragma unroll 8
+        for (int j = 0; j < n; ++j) lo += list[j] > k ? 1 : 0;
+        return lo;
+    }
     while (n > 0) {
         const int half = n >> 1;
         const bool above = list[lo + half] > k;

@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2609_39137_amd import binding as B
 from paper_2609_39137_amd import synth
 from paper_2609_39137_amd.pipeline import RouterStep
@@ -36,6 +37,24 @@ def test_tilings_of_one_order_agree(variant, ref, T, d, E, K):
     got = run_router(x, W, b, K, variant=variant)
     equal(got, want)
     check_invariants(*got[:3], T, E, K)
+
+
+# the slice merge against the oracle's selection on the kernel's own scores, bit
+# for bit: 3 to 8 slices, list lengths that are scanned and that are searched,
+# both merge kernels (up to 64 candidates per token and more), and ties that are
+# decided by the index across slices
+@pytest.mark.parametrize("E,variant", [(640, 3), (1024, 8), (800, 4), (1024, 4)])
+@pytest.mark.parametrize("K", [1, 7, 8, 9, 10, 11, 12, 15, 16, 17, 24, 32])
+def test_slice_merge_matches_the_oracle(E, variant, K):
+    T, d = 150, 64
+    x, W = synth.normal_router_inputs(T, d, E, seed=E + K, w_std=0.05)
+    for ties in (False, True):
+        if ties:
+            W[::3] = W[0]
+        b = synth.bias(E, "zero" if ties else "small", seed=K)
+        idx, w, c, s = run_router(x, W, b, K, variant=variant)
+        for got, want in zip((idx, w, c), oracle.select(s, b, K)):
+            np.testing.assert_array_equal(got.view(np.uint32), want.view(np.uint32))
 
 
 def resolved(T, E):
