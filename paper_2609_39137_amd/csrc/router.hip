@@ -450,27 +450,52 @@ __global__ __launch_bounds__(WAVES * 64) void router16_kernel(RouterArgs a, int 
     select_epilogue<EC, SM>(a, NS, slice, tok0, smem, breg, store_pass);
 }
 
-// How many of a slice's n rank-ordered (descending) keys are above k.  The
-// lists come sorted out of the epilogue, so a binary search finds it, but its
-// probes depend on each other and, with lists of 8 or 16 keys, meet in a few
-// LDS banks; a scan of a short list reads 8 keys at once.  Whole steps, scan
-// against search, us: n = 8: E = 800 T = 8192 d = 64 61.3 / 73.0, fp32 E = 1024 T =
-// 2560 d = 32 51.2 / 66.7; n = 10: search 1.01 to 1.03 times the scan; n = 16: 1.01
-// to 1.10; n = 12 and 14: 0.96 and 0.89 on average over 4 slices; n > 16: 0.99.
-__device__ __forceinline__ int count_above(const unsigned long long* list, int n, unsigned long long k) {
-    int lo = 0;
-    if (n <= 10 || n == 16) {  // uniform: the list length of the launch
-#pragma unroll 8
-        for (int j = 0; j < n; ++j) lo += list[j] > k ? 1 : 0;
-        return lo;
+// The rank of a candidate with key k: r, its rank in its own slice sl, plus the
+// keys above k in the other slices' rank-ordered (descending) lists of KL keys,
+// slice o's at list + o KL.  The lists come sorted out of the epilogue, so a
+// binary search finds that number, but its probes depend on each other and, with
+// lists of 8 or 16 keys, meet in a few LDS banks; a scan of a short list reads 8
+// keys at once.  Whole steps, scan against search, us: KL = 8: E = 800 T = 8192
+// d = 64 61.3 / 73.0, fp32 E = 1024 T = 2560 d = 32 51.2 / 66.7; KL = 10: search 1.01
+// to 1.03 times the scan; KL = 16: 1.01 to 1.10; KL = 12 and 14: 0.96 and 0.89 on
+// average over 4 slices; KL > 16: 0.99.  The form is chosen outside the loop
+// over the slices.
+__device__ __forceinline__ int merged_rank(const unsigned long long* list, int NS, int KL, int sl, int r,
+                                           unsigned long long k) {
+    int rank = r;
+    if (KL <= 10 || KL == 16) {  // uniform: the list length of the launch
+        for (int o = 0; o < NS; ++o) {
+            if (o == sl) continue;
+            const unsigned long long* lo = list + o * KL;
+            int j = 0;
+            for (; j + 8 <= KL; j += 8) {
+                unsigned long long q[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) q[i] = lo[j + i];
+                // all reads before the first compare, which the scheduler
+                // would else pair one by one
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) rank += q[i] > k ? 1 : 0;
+            }
+#pragma unroll 1
+            for (; j < KL; ++j) rank += lo[j] > k ? 1 : 0;
+        }
+        return rank;
     }
-    while (n > 0) {
-        const int half = n >> 1;
-        const bool above = list[lo + half] > k;
-        lo = above ? lo + half + 1 : lo;
-        n = above ? n - half - 1 : half;
+    for (int o = 0; o < NS; ++o) {
+        if (o == sl) continue;
+        const unsigned long long* lo = list + o * KL;
+        int below = 0, n = KL;
+        while (n > 0) {
+            const int half = n >> 1;
+            const bool above = lo[below + half] > k;
+            below = above ? below + half + 1 : below;
+            n = above ? n - half - 1 : half;
+        }
+        rank += below;
     }
-    return lo;
+    return rank;
 }
 
 // Merge the slices' rank-ordered candidate lists into the final Top-K, compute
@@ -513,8 +538,7 @@ __global__ __launch_bounds__(kMergeThreads) void router_merge_kernel(RouterArgs 
         __syncthreads();
         int rank = r;
         if (act) {
-            for (int o = 0; o < NS; ++o)
-                if (o != sl) rank += count_above(key + tt * per_tok + o * KL, KL, k);
+            rank = merged_rank(key + tt * per_tok, NS, KL, sl, r, k);
             if (rank < K) {
                 sel[tt * K + rank] = s;
                 a.idx[tok * K + rank] = e;
@@ -640,9 +664,7 @@ __global__ __launch_bounds__(kTileThreads) void router_merge_tile_kernel(RouterA
                 const int t = c / NSK, pos = c - t * NSK;
                 const int sl = pos / KL, r = pos - sl * KL;
                 const unsigned long long k = mk[c];
-                int rank = r;
-                for (int o = 0; o < NS; ++o)
-                    if (o != sl) rank += count_above(mk + t * NSK + o * KL, KL, k);
+                const int rank = merged_rank(mk + t * NSK, NS, KL, sl, r, k);
                 if (rank < K) {
                     msel[t * kMaxK + rank] = ms[c];
                     midx[t * kMaxK + rank] = (int)~(unsigned)k;
