@@ -164,6 +164,7 @@ struct RouterCall {
     unsigned* ticket;  // the merge's (multi-slice tilings) or the statistics kernel's ticket
     idb::AuxPartial* aux_partial;  // auxiliary-loss statistics: block records
     bool scored;                   // the scored path: launch_scores, then launch_select_step
+    float* scores;                 // scored: the [T][E] scores in the workspace
     char* pack_to;                 // scored: nullable, where a row-major router matrix is packed first
 };
 
@@ -230,7 +231,6 @@ idb_status prepare_router(const void* x, const void* W_g, idb_dtype dtype, idb_w
     a.ticket = need ? reinterpret_cast<unsigned*>(ws + 3 * part) : nullptr;
     a.alpha = nullptr;
     a.scores_t = nullptr;
-    a.scores = nullptr;
     a.softmax = aux ? 1 : 0;
     a.prob_part = nullptr;
     a.cnt_part = nullptr;
@@ -242,8 +242,9 @@ idb_status prepare_router(const void* x, const void* W_g, idb_dtype dtype, idb_w
     call->scored = own_workspace && workspace && aligned(workspace, 16) && workspace_bytes >= scored_need &&
                    use_scores(T, d, E, K, call->tiling, layout == IDB_WEIGHT_ROW_MAJOR);
     call->pack_to = nullptr;
+    call->scores = nullptr;
     if (call->scored) {
-        a.scores = reinterpret_cast<float*>(ws);
+        call->scores = reinterpret_cast<float*>(ws);
         call->ticket = reinterpret_cast<unsigned*>(ws + scored_need - 256);
         a.ticket = call->ticket;
         a.zero_counts = accumulate_counts ? 0 : 1;
@@ -280,7 +281,7 @@ idb_status enqueue_score_select(const RouterCall& c, int32_t accumulate_counts, 
             a.W = c.pack_to;
             a.w_packed = 1;
         }
-        return hip_result(idb::launch_scores(c.tiling, a, stream), "router score launch");
+        return hip_result(idb::launch_scores(c.tiling, a, c.scores, stream), "router score launch");
     }
     const int ns = idb::router_slices(c.tiling, c.args.E);
     if (ns <= 1 && !accumulate_counts && !c.args.cnt_part) {
@@ -376,7 +377,7 @@ idb_status idb_router_forward(const void* x, const void* W_g, idb_dtype dtype, i
     if (st != IDB_OK) return st;
     st = enqueue_score_select(c, accumulate_counts, stream);
     if (st != IDB_OK) return st;
-    if (c.scored) return hip_result(idb::launch_select_step(c.args, c.args.scores, nullptr, stream), "select launch");
+    if (c.scored) return hip_result(idb::launch_select_step(c.args, c.scores, nullptr, stream), "select launch");
     return hip_result(idb::launch_router_merge(c.tiling, c.args, nullptr, stream), "router merge launch");
 }
 
@@ -469,7 +470,7 @@ idb_status enqueue_merge_step(const RouterCall& c, const idb_controller_cfg* cfg
     k.status = state->status;
     k.stats = out_maxvio_minvio;
     k.ticket = c.ticket;
-    if (c.scored) return hip_result(idb::launch_select_step(c.args, c.args.scores, &k, stream), "select launch");
+    if (c.scored) return hip_result(idb::launch_select_step(c.args, c.scores, &k, stream), "select launch");
     return hip_result(idb::launch_router_merge(c.tiling, c.args, &k, stream), "router merge launch");
 }
 

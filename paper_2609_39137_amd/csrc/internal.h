@@ -89,7 +89,6 @@ struct RouterArgs {
     int zero_counts;  // workgroup 0 of the multi-slice kernel zeroes counts
     unsigned* ticket;  // nullable; workgroup 0 of the multi-slice kernel zeroes it
     float* dump;
-    float* scores;  // scored path: the [T][E] scores in the workspace, 16-byte aligned
     // multi-slice candidates in the workspace: [T][slices][KL], KL = K, or
     // K + 1 with alpha set
     float* cand_v;
@@ -143,10 +142,13 @@ hipError_t launch_router_score_select(const RouterTiling& t, const RouterArgs& a
 // finished counts (multi-slice tilings only).
 hipError_t launch_router_merge(const RouterTiling& t, const RouterArgs& a, const CtrlArgs* ctrl,
                                hipStream_t stream);
-// Scored path (scores.hip): s = sigmoid(W x) of every token into a.scores (and
-// a.dump), in the accumulation order of tiling t; zeroes counts (a.zero_counts)
-// and the ticket.
-hipError_t launch_scores(const RouterTiling& t, const RouterArgs& a, hipStream_t stream);
+// Scored path (scores.hip): s = sigmoid(W x) of every token into scores [T][E]
+// (16-byte aligned; and into a.dump), in the accumulation order of tiling t;
+// zeroes counts (a.zero_counts) and the ticket.  (Not a member of RouterArgs:
+// two more scalar registers of arguments made the one-slice router kernels spill
+// more of them; auxiliary-loss step, T = 65536, E = 256, K = 16, d = 64: 690 us
+// with it, 676 without.)
+hipError_t launch_scores(const RouterTiling& t, const RouterArgs& a, float* scores, hipStream_t stream);
 // Router matrix [E][d] (row_bytes per row) -> the packed A-operand layout.
 hipError_t launch_pack_weight(const void* W, void* P, int E, int64_t row_bytes, hipStream_t stream);
 

@@ -51,7 +51,7 @@ struct ScoreCfg {
 };
 
 template <bool M32, bool F32, bool PACKED, int WAVES, int TB, int EB, int D>
-__global__ __launch_bounds__(WAVES * 64) void score_kernel(RouterArgs a, int NS) {
+__global__ __launch_bounds__(WAVES * 64) void score_kernel(RouterArgs a, int NS, float* __restrict__ scores) {
     using C = ScoreCfg<M32, F32, WAVES, TB, EB, D>;
     using Acc = typename std::conditional<M32, floatx16, floatx4>::type;
     constexpr int NR = M32 ? 16 : 4;
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(WAVES * 64) void score_kernel(RouterArgs a, int NS)
                             make_float4(sigmoid_fast(acc[tb][eb][4 * r4]), sigmoid_fast(acc[tb][eb][4 * r4 + 1]),
                                         sigmoid_fast(acc[tb][eb][4 * r4 + 2]), sigmoid_fast(acc[tb][eb][4 * r4 + 3]));
                         const int64_t at = tok * E + e0 + 8 * r4 + 4 * lg;
-                        *reinterpret_cast<float4*>(a.scores + at) = s4;
+                        *reinterpret_cast<float4*>(scores + at) = s4;
                         if (a.dump) *reinterpret_cast<float4*>(a.dump + at) = s4;
                     }
                 }
@@ -236,22 +236,22 @@ __global__ __launch_bounds__(WAVES * 64) void score_kernel(RouterArgs a, int NS)
 }
 
 template <bool M32, bool F32, int WAVES, int TB, int EB, int D>
-hipError_t launch_scores_cfg(const RouterArgs& a, hipStream_t stream) {
+hipError_t launch_scores_cfg(const RouterArgs& a, float* scores, hipStream_t stream) {
     using C = ScoreCfg<M32, F32, WAVES, TB, EB, D>;
     const int NS = (a.E + C::BE - 1) / C::BE;
     const int64_t blocks = (a.T + C::BT - 1) / C::BT * NS;
     if (a.w_packed)
         hipLaunchKernelGGL((score_kernel<M32, F32, true, WAVES, TB, EB, D>), dim3((unsigned)blocks), dim3(C::NT), 0,
-                           stream, a, NS);
+                           stream, a, NS, scores);
     else
         hipLaunchKernelGGL((score_kernel<M32, F32, false, WAVES, TB, EB, D>), dim3((unsigned)blocks), dim3(C::NT), 0,
-                           stream, a, NS);
+                           stream, a, NS, scores);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_scores(const RouterTiling& t, const RouterArgs& a, hipStream_t stream) {
+hipError_t launch_scores(const RouterTiling& t, const RouterArgs& a, float* scores, hipStream_t stream) {
     // The largest tile that still gives the chip enough workgroups.  A larger
     // tile reads fewer operand bytes through L2 per score (what bounds these
     // launches once the chip is full), a smaller one fills more CUs.  us per
@@ -262,16 +262,16 @@ hipError_t launch_scores(const RouterTiling& t, const RouterArgs& a, hipStream_t
     // 24.4, 128 x 256 21.6, 32 x 128 26.1; at d = 4096, E = 256, T = 777: one block
     // per wave 11.9, 32 x 128 15.5, 64 x 128 19.8.
     auto blocks = [&](int bt, int be) { return (a.T + bt - 1) / bt * ((a.E + be - 1) / be); };
-    if (t.is_f32) return launch_scores_cfg<true, true, 1, 1, 1, 8>(a, stream);
+    if (t.is_f32) return launch_scores_cfg<true, true, 1, 1, 1, 8>(a, scores, stream);
     if (!tiling_is_16(t)) {
-        if (blocks(64, 128) >= kEnough32) return launch_scores_cfg<true, false, 4, 2, 1, 4>(a, stream);
-        return launch_scores_cfg<true, false, 1, 1, 1, 8>(a, stream);
+        if (blocks(64, 128) >= kEnough32) return launch_scores_cfg<true, false, 4, 2, 1, 4>(a, scores, stream);
+        return launch_scores_cfg<true, false, 1, 1, 1, 8>(a, scores, stream);
     }
-    if (blocks(128, 384) >= kFull) return launch_scores_cfg<false, false, 8, 8, 3, 2>(a, stream);
-    if (blocks(64, 192) >= kEnough16) return launch_scores_cfg<false, false, 4, 4, 3, 4>(a, stream);
-    if (blocks(64, 128) >= kEnough16) return launch_scores_cfg<false, false, 4, 4, 2, 4>(a, stream);
-    if (blocks(64, 64) >= kEnough16) return launch_scores_cfg<false, false, 4, 4, 1, 4>(a, stream);
-    return launch_scores_cfg<false, false, 1, 1, 1, 8>(a, stream);
+    if (blocks(128, 384) >= kFull) return launch_scores_cfg<false, false, 8, 8, 3, 2>(a, scores, stream);
+    if (blocks(64, 192) >= kEnough16) return launch_scores_cfg<false, false, 4, 4, 3, 4>(a, scores, stream);
+    if (blocks(64, 128) >= kEnough16) return launch_scores_cfg<false, false, 4, 4, 2, 4>(a, scores, stream);
+    if (blocks(64, 64) >= kEnough16) return launch_scores_cfg<false, false, 4, 4, 1, 4>(a, scores, stream);
+    return launch_scores_cfg<false, false, 1, 1, 1, 8>(a, scores, stream);
 }
 
 }  // namespace idb
