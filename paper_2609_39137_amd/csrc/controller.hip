@@ -69,22 +69,27 @@ __global__ __launch_bounds__(1024) void load_stats_kernel(const int32_t* __restr
 // L layers' updates in one launch, one workgroup per layer (Alg. 1 runs once
 // per MoE layer and iteration): counts, bias and e_prev [L][E], step and status
 // [L], stats [L][2] and diag [L][4] (both nullable).  The same bits as the
-// single-layer update.  Latency-bound; four waves divide the serial fp64
-// divisions and the ballots of the threshold search (one wave per layer: 15.7
-// us for 21 layers of 768 experts; 256 threads: 9.2 us).
-constexpr int kLayerThreads = 256;
+// single-layer update.  Up to kLayerWide layers latency-bound: four waves
+// divide the serial fp64 divisions and the ballots of the threshold search.
+// With more layers the chip is full and one wave per layer, which needs no
+// barrier and no LDS, costs less.  us with diagnostics, 256 and 64 threads: L =
+// 21, E = 768 8.5 / 11.7; L = 1024, E = 64 10.2 / 10.0, E = 1024 13.3 / 13.8; L = 1536,
+// E = 64 12.3 / 11.1, E = 1024 16.9 / 16.3; L = 4096, E = 64 23.6 / 14.4, E = 1024
+// 34.2 / 28.7; without: L = 1536, E = 768 8.4 / 9.4; L = 4096, E = 64 9.1 / 7.2.
+constexpr int kLayerWide = 1024;
 
-__global__ __launch_bounds__(kLayerThreads) void controller_layers_kernel(
+template <int NT>
+__global__ __launch_bounds__(NT) void controller_layers_kernel(
     const int32_t* __restrict__ counts, int E, float Ki, float Kd, int sign_mode, int center,
     float* __restrict__ bias, float* __restrict__ e_prev, int64_t* __restrict__ step, int32_t* __restrict__ status,
     double* __restrict__ stats, double* __restrict__ diag) {
-    constexpr int kPer = 1024 / kLayerThreads;
+    constexpr int kPer = 1024 / NT;
     __shared__ CtrlScratch sh;
     __shared__ DiagScratch dsh;
     const int64_t l = blockIdx.x;
     float b0[kPer], ep0[kPer];
     controller_load_state(bias + l * E, e_prev + l * E, E, b0, ep0);
-    controller_block<kPer>(counts + l * E, E, ctrl_tree_size(E), Ki, Kd, sign_mode, center, b0, ep0, bias + l * E,
+    controller_block<kPer, false, NT == 64>(counts + l * E, E, ctrl_tree_size(E), Ki, Kd, sign_mode, center, b0, ep0, bias + l * E,
                            e_prev + l * E, step + l, status + l, stats ? stats + 2 * l : nullptr, sh,
                            diag ? diag + 4 * l : nullptr, &dsh);
 }
@@ -102,8 +107,12 @@ hipError_t launch_controller_update(const int32_t* counts, int E, float Ki, floa
 hipError_t launch_controller_layers(const int32_t* counts, int L, int E, float Ki, float Kd, int sign_mode,
                                     int center, float* bias, float* e_prev, int64_t* step, int32_t* status,
                                     double* stats, double* diag, hipStream_t stream) {
-    hipLaunchKernelGGL(controller_layers_kernel, dim3((unsigned)L), dim3(kLayerThreads), 0, stream, counts, E, Ki, Kd,
-                       sign_mode, center, bias, e_prev, step, status, stats, diag);
+    if (L <= kLayerWide)
+        hipLaunchKernelGGL(controller_layers_kernel<256>, dim3((unsigned)L), dim3(256), 0, stream, counts, E, Ki, Kd,
+                           sign_mode, center, bias, e_prev, step, status, stats, diag);
+    else
+        hipLaunchKernelGGL(controller_layers_kernel<64>, dim3((unsigned)L), dim3(64), 0, stream, counts, E, Ki, Kd,
+                           sign_mode, center, bias, e_prev, step, status, stats, diag);
     return hipGetLastError();
 }
 

@@ -76,10 +76,11 @@ __device__ __forceinline__ long long split_total(int lo, int hi) { return (long 
 // h >= nt pair two leaves of one thread; levels nt/2 .. 64 pair the same lane
 // of two waves (through mem; wave 0 adds them in registers); the last six run
 // inside wave 0 (lane moves that add the same pairs).  Wave 0's lanes return
-// the root.  One barrier when more than one wave holds leaves.
-template <int kPer, class V>
+// the root.  One barrier when more than one wave holds leaves.  kOneWave: the
+// workgroup is one wave (mem unused).
+template <bool kOneWave, int kPer, class V>
 __device__ inline V block_tree_sum(V (&v)[kPer], int P, V* mem) {
-    const int i0 = threadIdx.x, nt = blockDim.x, lane = i0 & 63, wv = i0 >> 6;
+    const int i0 = threadIdx.x, nt = kOneWave ? 64 : blockDim.x, lane = i0 & 63, wv = kOneWave ? 0 : i0 >> 6;
 #pragma unroll
     for (int d = kPer / 2; d >= 1; d >>= 1)
         if (2 * d * nt <= P)
@@ -87,7 +88,7 @@ __device__ inline V block_tree_sum(V (&v)[kPer], int P, V* mem) {
             for (int q = 0; q < d; ++q) v[q] = v[q] + v[q + d];
     const int NP = P < nt ? P : nt;  // tree nodes left, node i0 in thread i0
     V a = v[0];
-    if (NP > 64) {
+    if (!kOneWave && NP > 64) {
         if (i0 >= 64 && i0 < NP) mem[i0] = a;
         __syncthreads();
         if (wv == 0) {
@@ -148,7 +149,9 @@ __device__ __forceinline__ void controller_load_state(const float* __restrict__ 
 // pairwise tree; NaN x 4 when the update does not run.
 // Reductions: exact integer sums/extrema (order-free); the centering mean with
 // the fixed pairwise tree of block_tree_sum, P = next power of two >= E.
-template <int kPer, bool kCoherentCounts = false>
+// kOneWave: the workgroup is one wave, which needs no LDS and no barrier (sh and
+// dsh unused).
+template <int kPer, bool kCoherentCounts = false, bool kOneWave = false>
 __device__ inline void controller_block(const int32_t* __restrict__ counts, int E, int P, float Ki, float Kd,
                                         int sign_mode, int center, const float (&b0)[kPer], const float (&ep0)[kPer],
                                         float* __restrict__ bias, float* __restrict__ e_prev,
@@ -156,8 +159,8 @@ __device__ inline void controller_block(const int32_t* __restrict__ counts, int 
                                         double* __restrict__ stats, CtrlScratch& sh, double* __restrict__ diag = nullptr,
                                         DiagScratch* dsh = nullptr) {
 #pragma clang fp contract(off)
-    const int i0 = threadIdx.x, nt = blockDim.x;
-    const int lane = i0 & 63, wv = i0 >> 6, nw = nt >> 6;
+    const int i0 = threadIdx.x, nt = kOneWave ? 64 : blockDim.x;
+    const int lane = i0 & 63, wv = kOneWave ? 0 : i0 >> 6, nw = nt >> 6;
     int n[kPer];
     SplitSum sum;
     int mx = INT32_MIN, mn = INT32_MAX;
@@ -178,17 +181,22 @@ __device__ inline void controller_block(const int32_t* __restrict__ counts, int 
     // each wave's four integers to LDS; every row then reduces the waves' partials
     int red[4] = {wave_reduce(sum.lo, AddOp{}), wave_reduce(sum.hi, AddOp{}), wave_reduce(mx, MaxOp{}),
                   wave_reduce(mn, MinOp{})};
-    if (lane == 0)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) sh.part[0][c][wv] = red[c];
-    __syncthreads();
     const int pw = lane & 15;
     const bool has = pw < nw;
+    if constexpr (!kOneWave) {
+        if (lane == 0)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sh.part[0][c][wv] = red[c];
+        __syncthreads();
+        red[0] = row_reduce(has ? sh.part[0][0][pw] : 0, AddOp{});
+        red[1] = row_reduce(has ? sh.part[0][1][pw] : 0, AddOp{});
+        red[2] = row_reduce(has ? sh.part[0][2][pw] : INT32_MIN, MaxOp{});
+        red[3] = row_reduce(has ? sh.part[0][3][pw] : INT32_MAX, MinOp{});
+    }
     // Total assignments S = E * nbar (Eq. pid-error).
-    const long long S = split_total(row_reduce(has ? sh.part[0][0][pw] : 0, AddOp{}),
-                                    row_reduce(has ? sh.part[0][1][pw] : 0, AddOp{}));
-    mx = row_reduce(has ? sh.part[0][2][pw] : INT32_MIN, MaxOp{});
-    mn = row_reduce(has ? sh.part[0][3][pw] : INT32_MAX, MinOp{});
+    const long long S = split_total(red[0], red[1]);
+    mx = red[2];
+    mn = red[3];
     if (stats && i0 == nt - 1) {
         // MaxVio, MinVio (Eq. vio): one fp64 division of an exact integer
         // numerator each; NaN for an empty batch.  (The last wave: wave 0
@@ -248,10 +256,15 @@ __device__ inline void controller_block(const int32_t* __restrict__ counts, int 
         float v[kPer];
 #pragma unroll
         for (int q = 0; q < kPer; ++q) v[q] = (i0 + q * nt < E) ? b[q] : 0.0f;
-        const float a = block_tree_sum(v, P, sh.tree);
-        if (i0 == 0) sh.root = a;
-        __syncthreads();
-        m = sh.root / (float)E;
+        if constexpr (kOneWave) {
+            const float a = block_tree_sum<true>(v, P, (float*)nullptr);
+            m = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, a))) / (float)E;
+        } else {
+            const float a = block_tree_sum<false>(v, P, sh.tree);
+            if (i0 == 0) sh.root = a;
+            __syncthreads();
+            m = sh.root / (float)E;
+        }
     }
     float nb[kPer];
 #pragma unroll
@@ -279,27 +292,32 @@ __device__ inline void controller_block(const int32_t* __restrict__ counts, int 
     }
     // The m = ceil(E/10) largest counts: their sum does not depend on how ties
     // are ranked, so it is sum(n_i > th) + (m - #{n_i > th}) th with th the
-    // m-th largest count, the largest v with #{n_i >= v} >= m, found two bits
-    // at a time from the top (counts are >= 0 here, mx the largest).
+    // m-th largest count, the largest v with #{n_i >= v} >= m, found from the
+    // top (counts are >= 0 here, mx the largest): two bits at a time where a step
+    // costs a barrier, one at a time (fewer ballots) in one wave.
     const int mtop = (E + 9) / 10;
     int th = 0;
-    const int top = (31 - __builtin_clz((unsigned)mx | 1u)) & ~1;  // the lower bit of the highest pair
-    for (int bit = top, bank = 0; bit >= 0; bit -= 2, bank ^= 1) {
-        int c[3] = {0, 0, 0};
+    constexpr int kBits = kOneWave ? 1 : 2, kTries = (1 << kBits) - 1;
+    const int top = (31 - __builtin_clz((unsigned)mx | 1u)) / kBits * kBits;  // the lowest of the highest bits
+    for (int bit = top, bank = 0; bit >= 0; bit -= kBits, bank ^= 1) {
+        int c[kTries] = {};
 #pragma unroll
         for (int q = 0; q < kPer; ++q)
 #pragma unroll
-            for (int t = 0; t < 3; ++t)
+            for (int t = 0; t < kTries; ++t)
                 c[t] += __builtin_popcountll(__builtin_amdgcn_ballot_w64(
                     i0 + q * nt < E && (unsigned)n[q] >= ((unsigned)th | ((unsigned)(t + 1) << bit))));
-        if (lane == 0)
+        if constexpr (!kOneWave) {
+            if (lane == 0)
 #pragma unroll
-            for (int t = 0; t < 3; ++t) dsh->wcnt[bank][t][wv] = c[t];
-        __syncthreads();  // the other bank was last read before the previous barrier
+                for (int t = 0; t < kTries; ++t) dsh->wcnt[bank][t][wv] = c[t];
+            __syncthreads();  // the other bank was last read before the previous barrier
+#pragma unroll
+            for (int t = 0; t < kTries; ++t) c[t] = row_reduce(has ? dsh->wcnt[bank][t][pw] : 0, AddOp{});
+        }
         int add = 0;
 #pragma unroll
-        for (int t = 0; t < 3; ++t)
-            add += row_reduce(has ? dsh->wcnt[bank][t][pw] : 0, AddOp{}) >= mtop ? 1 : 0;
+        for (int t = 0; t < kTries; ++t) add += c[t] >= mtop ? 1 : 0;
         th = (int)((unsigned)th | ((unsigned)add << bit));
     }
     SplitSum above;
@@ -313,16 +331,21 @@ __device__ inline void controller_block(const int32_t* __restrict__ counts, int 
     const int packed = gates << 16 | zeros;  // at most 1024 each
     int dred[4] = {wave_reduce(above.lo, AddOp{}), wave_reduce(above.hi, AddOp{}), wave_reduce(nabove, AddOp{}),
                    wave_reduce(packed, AddOp{})};
-    if (lane == 0)
+    double drift;
+    if constexpr (kOneWave) {
+        drift = block_tree_sum<true>(d, P, (double*)nullptr);
+    } else {
+        if (lane == 0)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) sh.part[1][c][wv] = dred[c];
-    const double drift = block_tree_sum(d, P, dsh->tree);
-    __syncthreads();
+            for (int c = 0; c < 4; ++c) sh.part[1][c][wv] = dred[c];
+        drift = block_tree_sum<false>(d, P, dsh->tree);
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < 4; ++c) dred[c] = row_reduce(has ? sh.part[1][c][pw] : 0, AddOp{});
+    }
     if (wv == 0) {
-        const long long sum_above = split_total(row_reduce(has ? sh.part[1][0][pw] : 0, AddOp{}),
-                                                row_reduce(has ? sh.part[1][1][pw] : 0, AddOp{}));
-        const int na = row_reduce(has ? sh.part[1][2][pw] : 0, AddOp{});
-        const int gz = row_reduce(has ? sh.part[1][3][pw] : 0, AddOp{});
+        const long long sum_above = split_total(dred[0], dred[1]);
+        const int na = dred[2], gz = dred[3];
         if (lane == 0) {
             const long long TOP = sum_above + (long long)(mtop - na) * (long long)th;
             diag[0] = (double)(gz >> 16) / (double)E;

@@ -90,6 +90,31 @@ def test_update_reductions_at_every_pool_size(E):
             np.testing.assert_array_equal(single.cpu().numpy(), oracle.load_stats(counts[l]))
 
 
+# above 1024 layers a layer is one wave instead of four: the same bits
+@pytest.mark.parametrize("E", [1, 2, 15, 17, 32, 64, 65, 129, 768, 1024])
+@pytest.mark.parametrize("mode,center", [(B.IDB_INTEGRAL_ERROR, True), (B.IDB_INTEGRAL_SIGN, False)])
+def test_many_layers_equal_few(E, mode, center):
+    rng = np.random.default_rng(E)
+    loads = np.stack([rng.integers(0, 2 ** 31, E, dtype=np.int64), rng.integers(0, 5, E), np.full(E, 2 ** 31 - 1),
+                      np.where(np.arange(E) % 3 == 0, 1000, 999), np.zeros(E), np.full(E, -1)]).astype(np.int32)
+    loads[1, 0] = 3
+    n, L = len(loads), 1025
+    cfg = B.ControllerCfg(E, 6e-3, 6e-3, mode, center)
+    outs = []
+    for layers in (n, L):
+        st = B.ControllerState(E, DEV, layers=layers)
+        stats, diag = (torch.zeros((layers, m), dtype=torch.float64, device=DEV) for m in (2, 4))
+        bare = B.ControllerState(E, DEV, layers=layers)  # without the statistics and diagnostics
+        for t in range(3):
+            counts = torch.from_numpy(np.roll(loads, t, axis=1)[np.arange(layers) % n]).to(DEV)
+            B.idb_controller_update_layers(counts, cfg, st, stats, diag)
+            B.idb_controller_update_layers(counts, cfg, bare)
+        outs.append([o.cpu().numpy() for o in (st.bias, st.e_prev, st.step, st.status, stats, diag, bare.bias,
+                                               bare.e_prev, bare.step, bare.status)])
+    for few, many in zip(*outs):
+        np.testing.assert_array_equal(many.view(np.uint8), few[np.arange(L) % n].view(np.uint8))
+
+
 def test_one_layer_equals_the_single_layer_update():
     E = 768
     cfg = B.ControllerCfg(E)
