@@ -139,8 +139,8 @@ __device__ __forceinline__ int row_count_greater(float m, std::integer_sequence<
 }
 
 // For each of this lane's G values: how many of the row's 16 G values are
-// strictly greater.  (A loop that rotates its copy by one lane at a time:
-// unrolled, the compares of all rotations are issued together and spill.)
+// strictly greater.  (The copy is rotated by one lane at a time; unrolled, 3 to
+// 4% of a small launch: T = 2048, E = 256, K = 12 9.4 us, 9.7 as a loop.)
 template <int G>
 __device__ __forceinline__ void row_count_greater(const float (&m)[G], int (&gt)[G]) {
     float o[G];
@@ -149,7 +149,7 @@ __device__ __forceinline__ void row_count_greater(const float (&m)[G], int (&gt)
         o[g] = m[g];
         gt[g] = 0;
     }
-#pragma unroll 1
+#pragma unroll
     for (int r = 0; r < 16; ++r) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
@@ -425,10 +425,15 @@ __global__ __launch_bounds__(64 * WAVES) void select_reg_kernel(RouterArgs a, co
 }
 
 // Workgroup shape.  Every workgroup flushes its histogram with one device
-// atomic per non-zero bin, so fewer, larger workgroups issue fewer atomics;
-// batches that would leave CUs without one use small workgroups instead.
+// atomic per non-zero bin, so fewer, larger workgroups issue fewer atomics to
+// the same few counters; small batches leave CUs idle that way and take smaller
+// ones.  us for 4, 8 and 16 waves: E = 768, K = 10: T = 64 8.2, 8.3, 9.0; E = 256,
+// K = 4: T = 256 6.8, 6.8, 7.5, T = 2048 9.0, 8.4, 8.3, T = 4096 11.8, 10.1, 8.7; E =
+// 96, K = 4: T = 4096 12.3, 10.0, 8.7.  Larger K: more work per token and group
+// maximum; E = 256, K = 16: T = 4096 -, 11.7, 12.4; E = 32, K = 32: T = 8192 -, 12.4, 13.7.
 constexpr int kRegWaves = 16;
-constexpr int kRegSmallWaves = 4;
+constexpr int kRegFewTokens = 256;        // up to here 4 waves
+constexpr int kRegTokensPerGroup = 2048;  // up to G times this 8 waves
 
 template <int NV, int WAVES, int G>
 hipError_t launch_select_waves(const RouterArgs& a, const float* scores, const CtrlArgs& ctrl, int cus,
@@ -454,8 +459,8 @@ hipError_t launch_select_reg(const RouterArgs& a, const float* scores, const Ctr
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         cus = 256;
-    if (a.T <= (int64_t)cus * 4 * kRegSmallWaves)
-        return launch_select_waves<NV, kRegSmallWaves, G>(a, scores, ctrl, cus, stream);
+    if (a.T <= kRegFewTokens) return launch_select_waves<NV, 4, G>(a, scores, ctrl, cus, stream);
+    if (a.T <= kRegTokensPerGroup * G) return launch_select_waves<NV, 8, G>(a, scores, ctrl, cus, stream);
     // the widest rows with several group maxima need more than the 128 VGPRs of
     // a 16-wave workgroup
     constexpr int waves = (NV >= 16 && G >= 2) || (NV >= 12 && G == 4) ? kRegWaves / 2 : kRegWaves;

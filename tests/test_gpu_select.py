@@ -94,11 +94,24 @@ def test_gate_weights_sum_to_one_and_ignore_bias():
     np.testing.assert_array_equal(w1, w2)
 
 
-@pytest.mark.parametrize("T,E,K", [(70001, 64, 4), (40001, 768, 10), (33000, 1024, 8)])
+# the last batch of each workgroup size (4, 8 and 16 waves) and the first of the
+# next, for each number of group maxima
+@pytest.mark.parametrize("T,K", [(256, 10), (257, 10), (2048, 10), (2049, 10), (256, 16), (257, 11), (4096, 16), (4097, 11),
+                                 (257, 17), (8192, 32), (8193, 17)])
+@pytest.mark.parametrize("E", [64, 100, 384, 768, 1000])
+def test_workgroup_sizes(T, E, K):
+    s = synth.scores(T, E, "beta", seed=T + E)
+    s[::5] = np.float32(0.25)  # lists that overflow among the others
+    check(s, synth.bias(E, "small", seed=K), K)
+
+
+@pytest.mark.parametrize("T,E,K", [(70001, 64, 4), (40001, 768, 10), (33000, 1024, 8), (16500, 256, 16), (16500, 1024, 11),
+                                   (16500, 512, 32), (16500, 768, 17), (33000, 128, 20)])
 def test_more_tiles_than_workgroups(T, E, K):
-    # more 64-token tiles than the launch has workgroups, so each walks
-    # several (grid-stride), ragged last tile; with E a multiple of 256 the
-    # full tiles take the load path without per-chunk conditions
+    # more tiles (of 32 or 64 tokens) than the launch has workgroups, so each
+    # walks several (grid-stride), ragged last tile, for each number of group
+    # maxima; with E a multiple of 256 the full tiles take the load path without
+    # per-chunk conditions
     s = synth.scores(T, E, "beta", seed=21 + E)
     b = synth.bias(E, "small", seed=22 + E)
     check(s, b, K)
