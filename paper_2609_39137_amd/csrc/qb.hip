@@ -15,9 +15,9 @@
 // (2.6 TB/s), 19.2 us once the biases have drifted off together (21.4 and 23.6
 // us with a threshold from the per-thread maxima, which also needed a full radix
 // select from r = T K / E > 512 or 1024 on); at T = 50001, E = 256, K = 8: 29.2 us
-// (1.8 TB/s; 145 us recomputing the keys in four radix passes).  Shorter than one piece or longer rows take an MSB-first radix
-// select with the keys recomputed from global memory in each of four passes of
-// 8-bit digits.
+// (1.8 TB/s; 145 us recomputing the keys in four radix passes).  Rows shorter
+// than one piece, and longer ones, take an MSB-first radix select with the keys
+// recomputed from global memory in each of four passes of 8-bit digits.
 //
 // With a counts pointer, workgroup 0 also writes MaxVio/MinVio of the step's
 // counts (Eq. vio), as the stand-alone statistics kernel does: exact integer
@@ -36,6 +36,11 @@ namespace {
 constexpr int kQbThreads = 512;  // the global-memory kernel's workgroup
 constexpr int kQbList = 4096;    // listed keys of a 512-thread workgroup
 constexpr int kFewKeys = 128;    // ranked by counting
+// Wanted ranks up to this many from the top are bracketed by the threads'
+// largest keys (rows of up to 8192 tokens); us, with them and with a sample: T =
+// 8192, E = 768, K = 10 (rank 107) 12.0 / 13.2; T = 4096, E = 64, K = 4 (rank 256)
+// 11.2 / 11.3; T = 4096, E = 256, K = 24 (rank 384) 15.2 / 10.4.
+constexpr int kTopRank = 160;
 
 // Order-preserving key of a float (after -0 -> +0): a < b iff key(a) < key(b).
 __device__ __forceinline__ unsigned order_key(float d) {
@@ -234,17 +239,25 @@ __device__ __forceinline__ void qb_stats_load(const int32_t* __restrict__ counts
 // NT threads, R keys per thread in registers (4 <= T <= R * NT): one read of
 // the row.  The wanted key is the r-th largest, r = T - k + 1.
 //   1. A sample of one key per thread, spread over the row, brackets it: the
-//      sample's order statistics 4 standard deviations above and 6 (and 4
-//      ranks, for the Poisson tail of small ones) below the expected rank, from
-//      a 16-bit radix select by one wave each (rounded outwards), give [lo, hi];
-//      hi is at most the row's largest key.
-//   2. The keys above hi are counted, those in [lo, hi] go to an LDS list
-//      (830 at T = 16384, r = 213; 2800 at T = 50001, r = 1562).
+//      sample's order statistics 4 standard deviations (and 1 rank) above and 6
+//      (and 5 ranks, for the Poisson tail of small ones) below the expected rank,
+//      from a 16-bit radix select by one wave each (rounded outwards), give
+//      [lo, hi]; no upper end where its rank would be below 1.  A bracket that
+//      would fill the list (it has no room for 10 deviations of the larger K / E on
+//      long rows) is narrowed to three quarters of it, still 3 deviations or
+//      more to each side: T = 65536, E = 64, K = 16 29 us, where the overflowing
+//      list and then the radix select took 54; T = 16384, E = 64, K = 31 16.5 / 23.8.
+//      Rows of up to 8192 tokens take a cheaper bracket where r <= kTopRank (the
+//      r-th largest of the threads' largest keys is a lower bound, as r keys
+//      reach it), and none for r > NT, where the radix select over 16 keys per
+//      thread costs less: T = 4096, E = 32, K = 16 11.2 us, 13.2 with the bracket.
+//   2. The keys above hi are counted, those in [lo, hi] go to an LDS list (864
+//      at T = 16384, r = 213; 3030 at T = 50001, r = 1562).
 //   3. The list's histogram over 1024 equal key intervals gives the interval of
 //      the wanted rank, again inside that interval while it holds many keys
 //      (margins of biases that have drifted together lie close), until its few
 //      keys are ranked by counting or it is a single key.
-// When the bracket misses (the sample does not bind the row) or the list
+// When the bracket misses (the sample does not bind the row) or the list still
 // overflows, a radix select over the registers takes over: the result is exact
 // in every case.
 // Bound by reading the row, then by the barriers of the three steps.
@@ -312,153 +325,177 @@ void qb_update_reg_kernel(const float* __restrict__ scores_t, const float* __res
         hi_s = ~0u;
         max_s = 0u;
     }
-    if ((unsigned)T > LIST / 2) {  // else the whole row goes to the list
+    const bool whole = (unsigned)T <= LIST / 2;  // the whole row goes to the list
+    const bool direct = R <= 16 && !whole && r_top > (unsigned)NT;
+    if (!whole && !direct) {
         // 1. the bracket; only slots that hold a token of every thread sampled
-        const int full = T / (4 * NT);  // whole rounds of pieces
-        const int slot = full > 0 ? tid % (4 * full) : 3;
-        const int ns = pieces < NT ? pieces : NT;
+        // (T > LIST / 2: at least one whole round of pieces)
+        const bool tops = R <= 16 && r_top <= (unsigned)kTopRank;
+        const int slot = tid % (4 * (T / (4 * NT)));
         unsigned mine = 0u;
+        if (tops) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) mine = r == slot ? key[r] : mine;
+            for (int r = 0; r < R; ++r) mine = key[r] > mine ? key[r] : mine;
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r) mine = r == slot ? key[r] : mine;
+        }
         sample[tid] = mine;
         __syncthreads();
-        const float share = (float)r_top / (float)T;
-        const float mid = share * (float)ns, dev = sqrtf(mid * (1.0f - share));
-        const int hi_rank = (int)(mid - 4.0f * dev - 1.0f), lo_rank = (int)(mid + 6.0f * dev) + 5;  // from the top
-        if (wave == 0 && lo_rank <= ns) {
-            const unsigned v = wave_select_reg<NT / 64, 16>(sample, (unsigned)ns, (unsigned)(ns - lo_rank + 1),
+        int hi_rank, lo_rank;  // from the top
+        if (tops) {
+            hi_rank = 0;
+            lo_rank = (int)r_top;
+        } else {
+            const float share = (float)r_top / (float)T;
+            const float mid = share * (float)NT, dev = sqrtf(mid * (1.0f - share));
+            hi_rank = (int)(mid - 4.0f * dev - 1.0f);
+            lo_rank = (int)(mid + 6.0f * dev) + 5;
+            const float most = 0.75f * (float)LIST * (float)NT / (float)T;  // sampled keys
+            if ((float)(lo_rank - (hi_rank > 0 ? hi_rank : 0)) > most) {
+                hi_rank = (int)(mid - 0.5f * most);
+                lo_rank = (int)(mid + 0.5f * most) + 1;
+            }
+        }
+        if (wave == 0 && lo_rank <= NT) {
+            const unsigned v = wave_select_reg<NT / 64, 16>(sample, (unsigned)NT, (unsigned)(NT - lo_rank + 1),
                                                             hist[0]);
             if (lane == 0 && v > 1u) lo_s = v;
         }
         if (wave == 1 && hi_rank >= 1) {
-            const unsigned v = wave_select_reg<NT / 64, 16>(sample, (unsigned)ns, (unsigned)(ns - hi_rank + 1),
+            const unsigned v = wave_select_reg<NT / 64, 16>(sample, (unsigned)NT, (unsigned)(NT - hi_rank + 1),
                                                             hist[1]);
             if (lane == 0) hi_s = v | 0xffffu;
         }
     }
-    __syncthreads();
-    const unsigned lo = lo_s, hi = hi_s;
-    // 2. counts above and inside, packed for one scan over the wave; one LDS
-    // atomic per wave for its place in the list
-    unsigned c = 0u, mx = 0u;
+    bool found = false;
+    if (!direct) {
+        __syncthreads();
+        const unsigned lo = lo_s, hi = hi_s;
+        // 2. counts above and inside, packed for one scan over the wave; one LDS
+        // atomic per wave for its place in the list
+        unsigned c = 0u, mx = 0u;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        c += key[r] > hi ? 0x10000u : key[r] >= lo ? 1u : 0u;
-        mx = key[r] > mx ? key[r] : mx;
-    }
-    if (hi == ~0u) {
-        // the row's largest key, one LDS atomic per wave
-        auto up = [](unsigned a, unsigned b) { return a > b ? a : b; };
-        mx = up(mx, (unsigned)row_rot<8>((int)mx));
-        mx = up(mx, (unsigned)row_rot<4>((int)mx));
-        mx = up(mx, (unsigned)row_rot<2>((int)mx));
-        mx = up(mx, (unsigned)row_rot<1>((int)mx));
-        const unsigned wmax = up(up((unsigned)__builtin_amdgcn_readlane((int)mx, 0),
-                                    (unsigned)__builtin_amdgcn_readlane((int)mx, 16)),
-                                 up((unsigned)__builtin_amdgcn_readlane((int)mx, 32),
-                                    (unsigned)__builtin_amdgcn_readlane((int)mx, 48)));
-        if (lane == 0) atomicMax(&max_s, wmax);
-    }
-    unsigned incl = c;
+        for (int r = 0; r < R; ++r) {
+            c += key[r] > hi ? 0x10000u : key[r] >= lo ? 1u : 0u;
+            mx = key[r] > mx ? key[r] : mx;
+        }
+        if (hi == ~0u) {
+            // the row's largest key, one LDS atomic per wave
+            auto up = [](unsigned a, unsigned b) { return a > b ? a : b; };
+            mx = up(mx, (unsigned)row_rot<8>((int)mx));
+            mx = up(mx, (unsigned)row_rot<4>((int)mx));
+            mx = up(mx, (unsigned)row_rot<2>((int)mx));
+            mx = up(mx, (unsigned)row_rot<1>((int)mx));
+            const unsigned wmax = up(up((unsigned)__builtin_amdgcn_readlane((int)mx, 0),
+                                        (unsigned)__builtin_amdgcn_readlane((int)mx, 16)),
+                                     up((unsigned)__builtin_amdgcn_readlane((int)mx, 32),
+                                        (unsigned)__builtin_amdgcn_readlane((int)mx, 48)));
+            if (lane == 0) atomicMax(&max_s, wmax);
+        }
+        unsigned incl = c;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const unsigned up = __shfl_up(incl, o);
-        if (lane >= o) incl += up;
-    }
-    unsigned base = 0u;
-    if (lane == 63) {
-        base = atomicAdd(&nlist, incl & 0xffffu);
-        atomicAdd(&nabove, incl >> 16);
-    }
-    unsigned pos = __shfl(base, 63) + (incl & 0xffffu) - (c & 0xffffu);
-    if ((c & 0xffffu) != 0u) {
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned up = __shfl_up(incl, o);
+            if (lane >= o) incl += up;
+        }
+        unsigned base = 0u;
+        if (lane == 63) {
+            base = atomicAdd(&nlist, incl & 0xffffu);
+            atomicAdd(&nabove, incl >> 16);
+        }
+        unsigned pos = __shfl(base, 63) + (incl & 0xffffu) - (c & 0xffffu);
+        if ((c & 0xffffu) != 0u) {
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (key[r] >= lo && key[r] <= hi) {
-                if (pos < LIST) list[pos] = key[r];
-                ++pos;
-            }
-    }
-    unsigned* bins = &hist[0][0];
-    for (int i = tid; i < BINS; i += NT) bins[i] = 0u;
-    __syncthreads();
-    const unsigned n = nlist, above = nabove;
-    if (above < r_top && r_top <= above + n && n <= LIST) {
-        // 3. intervals of 2^sh keys from `from`
-        unsigned want = r_top - above;  // rank from the top of the list
-        unsigned from = lo, m;
-        const unsigned span = (hi == ~0u ? max_s : hi) - lo;
-        int sh = span < (unsigned)BINS ? 0 : 22 - __builtin_clz(span);
-        unsigned width = ~0u;  // keys from `from` on that are looked at, less one
-        for (;;) {
-            for (unsigned i = tid; i < n; i += NT) {
-                const unsigned u = list[i];
-                if (u >= from && u - from <= width) atomicAdd(&bins[(u - from) >> sh], 1u);
-            }
-            __syncthreads();
-            if (wave == 0) {
-                // lane l owns the 16 bins below BINS - 16 l
-                const unsigned* own = bins + BINS - 16 * (lane + 1);
-                unsigned cnt[16], tot = 0u;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    cnt[i] = own[i];
-                    tot += cnt[i];
+            for (int r = 0; r < R; ++r)
+                if (key[r] >= lo && key[r] <= hi) {
+                    if (pos < LIST) list[pos] = key[r];
+                    ++pos;
                 }
-                unsigned sum = tot;
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const unsigned up = __shfl_up(sum, o);
-                    if (lane >= o) sum += up;
+        }
+        unsigned* bins = &hist[0][0];
+        for (int i = tid; i < BINS; i += NT) bins[i] = 0u;
+        __syncthreads();
+        const unsigned n = nlist, above = nabove;
+        found = above < r_top && r_top <= above + n && n <= LIST;
+        if (found) {
+            // 3. intervals of 2^sh keys from `from`
+            unsigned want = r_top - above;  // rank from the top of the list
+            unsigned from = lo, m;
+            const unsigned span = (hi == ~0u ? max_s : hi) - lo;
+            int sh = span < (unsigned)BINS ? 0 : 22 - __builtin_clz(span);
+            unsigned width = ~0u;  // keys from `from` on that are looked at, less one
+            for (;;) {
+                for (unsigned i = tid; i < n; i += NT) {
+                    const unsigned u = list[i];
+                    if (u >= from && u - from <= width) atomicAdd(&bins[(u - from) >> sh], 1u);
                 }
-                unsigned run = sum - tot;
-                if (run < want && want <= sum) {
+                __syncthreads();
+                if (wave == 0) {
+                    // lane l owns the 16 bins below BINS - 16 l
+                    const unsigned* own = bins + BINS - 16 * (lane + 1);
+                    unsigned cnt[16], tot = 0u;
 #pragma unroll
-                    for (int i = 15; i >= 0; --i) {
-                        if (run < want && want <= run + cnt[i]) {
-                            pick[0] = (unsigned)(BINS - 16 * (lane + 1) + i);
-                            pick[1] = run;
-                            pick[2] = cnt[i];
+                    for (int i = 0; i < 16; ++i) {
+                        cnt[i] = own[i];
+                        tot += cnt[i];
+                    }
+                    unsigned sum = tot;
+#pragma unroll
+                    for (int o = 1; o < 64; o <<= 1) {
+                        const unsigned up = __shfl_up(sum, o);
+                        if (lane >= o) sum += up;
+                    }
+                    unsigned run = sum - tot;
+                    if (run < want && want <= sum) {
+#pragma unroll
+                        for (int i = 15; i >= 0; --i) {
+                            if (run < want && want <= run + cnt[i]) {
+                                pick[0] = (unsigned)(BINS - 16 * (lane + 1) + i);
+                                pick[1] = run;
+                                pick[2] = cnt[i];
+                            }
+                            run += cnt[i];
                         }
-                        run += cnt[i];
                     }
                 }
+                __syncthreads();
+                from += pick[0] << sh;
+                want -= pick[1];
+                m = pick[2];
+                if (sh == 0 || m <= (unsigned)kFewKeys) break;
+                // the next histogram covers this interval alone
+                for (int i = tid; i < BINS; i += NT) bins[i] = 0u;
+                width = (1u << sh) - 1u;
+                sh = sh > 10 ? sh - 10 : 0;
+                __syncthreads();
             }
-            __syncthreads();
-            from += pick[0] << sh;
-            want -= pick[1];
-            m = pick[2];
-            if (sh == 0 || m <= (unsigned)kFewKeys) break;
-            // the next histogram covers this interval alone
-            for (int i = tid; i < BINS; i += NT) bins[i] = 0u;
-            width = (1u << sh) - 1u;
-            sh = sh > 10 ? sh - 10 : 0;
-            __syncthreads();
-        }
-        if (sh == 0) {
-            if (tid == 0) result_s = from;  // one key value per interval
-        } else {
-            for (unsigned i = tid; i < n; i += NT) {
-                const unsigned u = list[i];
-                if (u >= from && (u - from) >> sh == 0u) sample[atomicAdd(&nsmall, 1u)] = u;
-            }
-            __syncthreads();
-            // every thread ranks one key: the wanted one has fewer than
-            // `want` keys above it and at least `want` not below it
-            if (tid < (int)m) {
-                const unsigned u = sample[tid];
-                unsigned gt = 0u, ge = 0u;
-                for (unsigned i = 0; i < m; ++i) {
-                    const unsigned o = sample[i];
-                    gt += o > u ? 1u : 0u;
-                    ge += o >= u ? 1u : 0u;
+            if (sh == 0) {
+                if (tid == 0) result_s = from;  // one key value per interval
+            } else {
+                for (unsigned i = tid; i < n; i += NT) {
+                    const unsigned u = list[i];
+                    if (u >= from && (u - from) >> sh == 0u) sample[atomicAdd(&nsmall, 1u)] = u;
                 }
-                if (gt < want && want <= ge) result_s = u;  // equal keys write the same value
+                __syncthreads();
+                // every thread ranks one key: the wanted one has fewer than
+                // `want` keys above it and at least `want` not below it
+                if (tid < (int)m) {
+                    const unsigned u = sample[tid];
+                    unsigned gt = 0u, ge = 0u;
+                    for (unsigned i = 0; i < m; ++i) {
+                        const unsigned o = sample[i];
+                        gt += o > u ? 1u : 0u;
+                        ge += o >= u ? 1u : 0u;
+                    }
+                    if (gt < want && want <= ge) result_s = u;  // equal keys write the same value
+                }
             }
+            __syncthreads();
+            if (tid == 0) write_bias(bias, j, result_s, rho);
         }
-        __syncthreads();
-        if (tid == 0) write_bias(bias, j, result_s, rho);
-    } else {
+    }
+    if (!found) {
         // full radix select over the registers; the empty slots rank lowest
         unsigned kleft = k + (unsigned)(R * NT - T), prefix = 0u, mask = 0u;
         for (int shift = 24; shift >= 0; shift -= 8) {

@@ -199,8 +199,11 @@ def qb_case(T, E, kind):
 
 # row lengths around the pieces of four tokens, the whole-row list, the keys
 # per thread of each kernel form (8192, 16384, 32768 and 65536 tokens) and the
-# form beyond them; ranks from T / 96 to T / 2
-@pytest.mark.parametrize("T,E,K", [(3, 32, 4), (4, 32, 4), (5, 32, 16), (7, 96, 1), (2048, 32, 8), (2049, 32, 8),
+# form beyond them; ranks from T / 96 to T / 2, and at the edges of the bracket by
+# the threads' largest keys (160, 161) and of the direct radix select (512, 513);
+# brackets that are narrowed to what the list holds
+@pytest.mark.parametrize("T,E,K", [(5088, 32, 1), (5120, 32, 1), (4088, 8, 1), (4096, 8, 1), (16384, 8, 4), (65536, 16, 4),
+                                   (3, 32, 4), (4, 32, 4), (5, 32, 16), (7, 96, 1), (2048, 32, 8), (2049, 32, 8),
                                    (8191, 32, 16), (8193, 64, 1), (16383, 32, 2), (16385, 32, 8), (32769, 8, 4),
                                    (50001, 32, 1), (65535, 16, 2), (65536, 8, 4), (65537, 8, 2)])
 @pytest.mark.parametrize("kind", ["beta", "sorted", "block", "constant", "levels", "drifted"])
