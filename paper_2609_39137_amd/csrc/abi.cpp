@@ -106,31 +106,50 @@ size_t router_ws_bytes(int64_t T, int32_t E, int32_t K, const idb::RouterTiling&
 // materialised scores (scores.hip, then the selection of select.hip) instead
 // of the fused tiling t.  It has small tiles for small batches and a selection
 // that keeps its speed for large K, but writes and reads T x E scores, so the
-// fused kernel takes over as the batch grows.  The lines below are where whole
-// steps cross (scored against fused, us, d = 2048 unless said):
-//  - fp32: E = 256 T = 8192 45.5 / 53.9, T = 12288 60.5 / 54.5; E = 64 T = 32768
-//    46.5 / 55.0 (d = 512)
-//  - 128-expert tiles: E = 128 T = 16384 32.4 / 38.9, T = 32768 61.7 / 43.9
-//  - K = 8 on 32-token tiles: E = 768 T = 2048 27.2 / 34.1, T = 2560 31.2 / 33.9,
-//    T = 4096 37.2 / 35.0; E = 256 T = 2560 22.6 / 25.5, T = 4096 28.1 / 26.5; with
-//    d = 512, where the selection weighs more, E = 768 T = 1024 17.3 / 18.9, T = 2048
-//    21.4 / 19.3
-//  - K > 12 (the fused lists overflow, the slice merge grows): K = 16 E = 768
-//    T = 50001 245 / 359; E = 512 T = 16384 70.4 / 71.4; E = 1024 T = 16384 142 / 139
+// fused kernel takes over as the batch grows, and sooner the less contraction
+// there is to gain from (small d).  The lines lie where whole steps cross or,
+// where the lists of the fused epilogue make its time jump with the data, where
+// no measured shape lost to the fused kernels (scored / fused, us):
+//  - fp32: E = 256 T = 8192 45.5 / 53.9, T = 12288 60.5 / 54.5 (d = 2048); E = 128
+//    T = 16384 d = 256 33.7 / 36.8, d = 64 27.0 / 24.9; E = 64 T = 32768 d = 64 29.4 / 26.7
+//  - 128-expert tiles: E = 128 T = 16384 d = 2048 32.4 / 38.9, d = 64 21.9 / 21.2;
+//    T = 18000, where the selection starts a second round, d = 2048 40.4 / 39.0, d = 512
+//    27.1 / 25.6; E = 64 T = 20480 is level; several slices: E = 896 T = 4097 d = 64
+//    K = 1 23.9 / 22.4, K = 4 26.0 / 34.5, T = 6000 K = 4 29.4 / 46.6
+//  - K = 8 on 32-token tiles: d = 2048 E = 768 T = 2048 27.2 / 34.1, T = 2560 31.2 /
+//    33.9, T = 4096 37.2 / 35.0; E = 256 T = 2560 22.6 / 25.5, T = 4096 28.1 / 26.5;
+//    d = 512 E = 768 T = 1024 17.3 / 18.9, T = 2048 21.4 / 19.3
+//  - K > 12 (the fused lists overflow from about K = 14 on, the slice merge
+//    grows): 384-expert tiles: K = 16 E = 768 T = 16384 d = 2048 71 / 139, E = 384
+//    T = 65536 d = 64 65 / 171; K = 14 E = 384 T = 24000 d = 64 42 / 49, d = 4096 129 / 103;
+//    K = 13 E = 384 T = 8192 d = 1024 32 / 26, T = 32768 56 / 51; K = 13 E = 768 T =
+//    32768 d = 2048 124 / 134, T = 65536 d = 1024 181 / 163, d = 64 85 / 98.  256-expert
+//    tiles: K = 16 one slice, E = 256 T = 12000 d = 64 28.9 / 27.7; four slices, E = 1024
+//    T = 12000 K = 13 d = 256 53.9 / 68.4.  K > 20: E = 256 T = 16384 K = 21 d = 1024 39 / 138,
+//    E = 1024 T = 16384 K = 32 d = 256 73 / 954
 //  - a row-major router matrix, which the fused kernels read at a quarter to
-//    half of the packed rate and the scored path packs first: E = 256 T = 16384
-//    45.6 / 51.1, T = 32768 91.7 / 59.7; E = 768 T = 8192 51.9 / 70.9; E = 1024 T = 8192
-//    66.5 / 64.7
+//    half of the packed rate and the scored path packs first: K = 8, d = 1024
+//    E = 256 T = 16384 35 / 35, E = 768 T = 8192 39 / 43, E = 1024 T = 6000 40 / 48;
+//    d = 768 E = 256 T = 12000 31 / 29, E = 768 T = 8192 37 / 37; d = 384 E = 256 T = 8192
+//    24 / 22, E = 768 T = 2561 25 / 26, T = 8192 37 / 29; d = 256 E = 768 T = 3000 25.0 / 23.5
 bool use_scores(int64_t T, int32_t d, int32_t E, int32_t K, const idb::RouterTiling& t, bool row_major) {
+    constexpr int64_t kMi = int64_t(1) << 20;
     const int64_t n = T * E;
-    if (n > (int64_t(64) << 20)) return false;  // 256 MB of scores
-    if (t.is_f32) return n <= (int64_t(2) << 20);
-    if (t.id == 4) return E <= 128 ? T <= 20480 : n <= (int64_t(6) << 20);
-    if (K > 12) {
-        if (K > 20 || idb::tiling_is_16(t)) return true;
-        return n <= (int64_t(idb::router_slices(t, E) > 1 ? 12 : 3) << 20);
+    if (n > 64 * kMi) return false;  // 256 MB of scores
+    const bool one_slice = idb::router_slices(t, E) <= 1;
+    if (t.is_f32) return n <= (d >= 256 ? 2 * kMi : 3 * kMi / 2);
+    if (t.id == 4) {
+        if (E <= 64) return T <= 20480;
+        if (E <= 128) return T <= (d >= 256 ? 16384 : 14336);
+        return n <= (K > 1 ? 6 * kMi : 3 * kMi);
     }
-    if (row_major && n <= (int64_t(6) << 20)) return true;
+    if (K > 12) {
+        if (K > 20) return true;
+        if (!idb::tiling_is_16(t)) return n <= (one_slice ? 3 * kMi : 12 * kMi);
+        if (one_slice) return K > (d >= 2048 ? 14 : 13) || n <= 3 * kMi;
+        return K > 13 || d < 1024 || n <= 32 * kMi;
+    }
+    if (row_major && d >= 384 && n <= (d >= 768 ? 6 * kMi : 2 * kMi)) return true;
     return T <= (d >= 1024 ? 2560 : 1280);
 }
 

@@ -31,10 +31,38 @@ def scored_bytes(T, E):
     (65537, 2048, 1024, 21, 0, 4, False, False),  # above 256 MB of scores
     (777, 4096, 256, 8, 0, 1, True, False),
     (24577, 4096, 256, 8, 0, 1, False, False),
-    (20480, 512, 128, 8, 0, 1, True, True),
-    (20481, 512, 128, 8, 0, 1, False, False),
+    (2730, 512, 768, 10, 0, 2, True, True),       # row-major only, smaller hidden sizes
+    (2731, 512, 768, 10, 0, 2, False, False),
+    (1280, 256, 768, 10, 0, 2, True, True),
+    (1281, 256, 768, 10, 0, 2, False, False),
+    (8192, 1024, 384, 13, 0, 1, True, True),      # K > 12, one slice
+    (8193, 1024, 384, 13, 0, 1, False, False),
+    (8193, 1024, 384, 14, 0, 1, True, True),
+    (8193, 2048, 384, 14, 0, 1, False, False),
+    (8193, 2048, 384, 15, 0, 1, True, True),
+    (12288, 64, 256, 20, 0, 1, True, True),
+    (12289, 64, 256, 20, 0, 1, False, False),
+    (12289, 64, 256, 21, 0, 1, True, True),
+    (43690, 1024, 768, 13, 0, 2, True, True),     # several slices
+    (43691, 1024, 768, 13, 0, 2, False, False),
+    (43691, 512, 768, 13, 0, 2, True, True),
+    (43691, 1024, 768, 14, 0, 2, True, True),
+    (12288, 64, 1024, 20, 0, 4, True, True),
+    (12289, 64, 1024, 20, 0, 4, False, False),
+    (16384, 512, 128, 8, 0, 1, True, True),       # 128-expert tiles
+    (16385, 512, 128, 8, 0, 1, False, False),
+    (14336, 64, 128, 8, 0, 1, True, True),
+    (14337, 64, 128, 8, 0, 1, False, False),
+    (20480, 512, 64, 8, 0, 1, True, True),
+    (20481, 512, 64, 8, 0, 1, False, False),
+    (3510, 64, 896, 1, 0, 7, True, True),
+    (3511, 64, 896, 1, 0, 7, False, False),
+    (7021, 64, 896, 2, 0, 7, True, True),
+    (7022, 64, 896, 2, 0, 7, False, False),
     (32768, 256, 64, 4, 1, 1, True, False),       # fp32 is never packed on the way
     (32769, 256, 64, 4, 1, 1, False, False),
+    (24576, 64, 64, 4, 1, 1, True, False),
+    (24577, 64, 64, 4, 1, 1, False, False),
 ])
 def test_workspace_covers_the_path_of_either_layout(T, d, E, K, dtype, slices, scored, packs):
     assert B.idb_router_variant_info(T, d, E, K, dtype, 0)["slices"] == slices
