@@ -73,10 +73,11 @@ def test_automatic_tiling_by_batch_size():
     assert resolved(2048, 1024) == 12 and resolved(2049, 1024) == 9
 
 
-# the last batch on one tile size and the first on the next: every token
-# they share has the same outputs
+# the last batch on one tile size of the fused tilings and the first on the next:
+# every token they share has the same outputs
 @pytest.mark.parametrize("T,E,K", [(8192, 768, 10), (4096, 768, 10), (4096, 1024, 16), (16384, 256, 8), (4096, 512, 3)])
 def test_a_token_s_outputs_do_not_depend_on_its_batch(T, E, K):
+    assert resolved(T, E) != resolved(T + 1, E)
     x, W = synth.normal_router_inputs(T + 1, 64, E, seed=E, w_std=0.05)
     b = synth.bias(E, "small", seed=2)
     small, large = run_router(np.ascontiguousarray(x[:T]), W, b, K), run_router(x, W, b, K)
@@ -86,22 +87,48 @@ def test_a_token_s_outputs_do_not_depend_on_its_batch(T, E, K):
     equal(large[:3], (si, sw, sc))
 
 
-# the scored path (variant 0: small batches, large K, row-major router matrices)
-# against the fused tiling of the same order, bit for bit: scores, selection,
-# counts over two microbatches, and the controller update; (T, d, E, K, dtype):
-# both MFMA shapes and fp32, every tile size, part tiles, fewer chunks than are
-# prefetched, odd chunk counts, padded expert blocks, every number of selection
-# groups, both sizes of selection workgroups, a packed-first row-major matrix
+# the tilings that batches of more than 4096 tokens run, against the oracle on
+# integer inputs (exact logits, a zero bias: the selection is decided identically)
+@pytest.mark.parametrize("T,E,K,tiling", [(4097, 768, 10, 10), (8193, 736, 4, 6), (4097, 256, 8, 9), (16385, 256, 3, 8),
+                                          (4097, 1024, 5, 8), (4100, 512, 8, 9), (4097, 384, 12, 10)])
+def test_tilings_of_large_batches_match_the_oracle(T, E, K, tiling):
+    x, W = synth.integer_router_inputs(T, 64, E, seed=T + E, dtype="bf16", w_shift=6)
+    rs = RouterStep(T, 64, E, K, torch.bfloat16, B.ControllerCfg(E))
+    rs.pack(to_dev(W))
+    assert rs.info["variant"] == tiling and not rs.uses_scores(packed=True)
+    rs.step(to_dev(x))
+    ref = oracle.ControllerState(E)
+    r_idx, r_w, r_c = oracle.router(x, W, ref.bias, K)
+    np.testing.assert_array_equal(rs.idx.cpu().numpy(), r_idx)
+    np.testing.assert_array_equal(rs.counts.cpu().numpy(), r_c)
+    np.testing.assert_allclose(rs.w.cpu().numpy(), r_w, rtol=2e-5)
+    oracle.controller(r_c, ref, rs.cfg.Ki, rs.cfg.Kd)
+    np.testing.assert_array_equal(rs.state.bias.cpu().numpy().view(np.uint32), ref.bias.view(np.uint32))
+    np.testing.assert_array_equal(rs.stats.cpu().numpy(), oracle.load_stats(r_c))
+
+
+# the scored path (RouterStep's automatic choice: small batches, large K,
+# row-major router matrices) against the fused tiling of the same order, bit for
+# bit: scores, selection, counts over two microbatches, and the controller
+# update; (T, d, E, K, dtype): both MFMA shapes and fp32, every tile size, part
+# tiles, fewer chunks than are prefetched, odd chunk counts, every number of
+# selection groups, the sizes of selection workgroups; then expert blocks that
+# do not divide E: 32x32 tiles of 64 x 128, 16x16 tiles of 64 x 64, 64 x 128, 64 x 192
+# and 128 x 384
 SCORED = [(1, 64, 32, 32, "bf16"), (16, 128, 768, 10, "bf16"), (17, 576, 384, 13, "bf16"),
           (257, 64, 768, 16, "bf16"), (1025, 448, 768, 10, "bf16"), (2100, 64, 768, 24, "bf16"),
           (4097, 64, 768, 20, "bf16"), (14500, 64, 768, 17, "bf16"), (33, 64, 64, 4, "bf16"),
           (777, 256, 256, 8, "bf16"), (1500, 192, 1024, 16, "bf16"), (700, 128, 640, 11, "bf16"),
-          (4100, 64, 1024, 32, "bf16"), (5000, 64, 512, 3, "bf16"), (31, 32, 64, 4, "f32"), (1000, 288, 128, 21, "f32"),
-          (4096, 256, 64, 1, "f32")]
+          (4100, 64, 1024, 32, "bf16"), (1200, 64, 512, 3, "bf16"), (31, 32, 64, 4, "f32"), (1000, 288, 128, 21, "f32"),
+          (4096, 256, 64, 1, "f32"),
+          (7700, 128, 96, 8, "bf16"), (900, 64, 736, 10, "bf16"), (1700, 64, 352, 16, "bf16"), (3500, 64, 352, 13, "bf16"),
+          (5100, 64, 352, 14, "bf16"), (14300, 64, 736, 14, "bf16"), (28600, 64, 352, 16, "bf16")]
+# a row-major matrix that is packed on the way, where a packed one takes the fused tiling
+ROW_MAJOR = [(2000, 448, 512, 8, "bf16"), (8000, 768, 736, 4, "bf16")]
 
 
-@pytest.mark.parametrize("packed", [False, True])
-@pytest.mark.parametrize("T,d,E,K,dtype", SCORED)
+@pytest.mark.parametrize("T,d,E,K,dtype,packed", [(*c, p) for c in SCORED for p in (False, True)] +
+                         [(*c, False) for c in ROW_MAJOR])
 @pytest.mark.parametrize("ties", [False, True])
 def test_scored_path_equals_the_fused_tiling(T, d, E, K, dtype, packed, ties):
     x, W = synth.normal_router_inputs(T, d, E, seed=T + K, dtype=dtype, w_std=0.05)
@@ -113,6 +140,7 @@ def test_scored_path_equals_the_fused_tiling(T, d, E, K, dtype, packed, ties):
     outs = []
     for variant in (0, fused):
         rs = RouterStep(T, d, E, K, xt.dtype, B.ControllerCfg(E), variant=variant)
+        assert rs.uses_scores(packed) == (variant == 0)
         rs.state.bias.copy_(torch.from_numpy(synth.bias(E, "zero" if ties else "small", seed=K)))
         Wa = None if packed else Wt
         if packed:

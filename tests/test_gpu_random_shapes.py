@@ -77,20 +77,23 @@ def test_router_step_random_shapes(T, d, E, K, sign, center, seed):
     Ki, Kd = 2.0 ** -7, 2.0 ** -6
     mode = B.IDB_INTEGRAL_SIGN if sign else B.IDB_INTEGRAL_ERROR
     x, W = synth.integer_router_inputs(T, d, E, seed=3000 + seed, dtype="bf16", w_shift=6)
-    rs = RouterStep(T, d, E, K, torch.bfloat16, B.ControllerCfg(E, Ki, Kd, mode, center), device=DEV)
     xt = torch.from_numpy(x.view(np.int16)).to(DEV).view(torch.bfloat16)
     Wt = torch.from_numpy(W.view(np.int16)).to(DEV).view(torch.bfloat16)
-    rs.step(xt, Wt)
-    torch.cuda.synchronize()
     ref = oracle.ControllerState(E)
     r_idx, r_w, r_c = oracle.router(x, W, ref.bias, K)
-    np.testing.assert_array_equal(rs.idx.cpu().numpy(), r_idx)
-    np.testing.assert_array_equal(rs.counts.cpu().numpy(), r_c)
-    np.testing.assert_allclose(rs.w.cpu().numpy(), r_w, rtol=2e-5)
     oracle.controller(r_c, ref, Ki, Kd, oracle.MODE_SIGN if sign else oracle.MODE_ERROR, center)
-    np.testing.assert_array_equal(rs.state.bias.cpu().numpy(), ref.bias)
-    np.testing.assert_array_equal(rs.state.e_prev.cpu().numpy(), ref.e_prev)
-    np.testing.assert_array_equal(rs.stats.cpu().numpy(), oracle.load_stats(r_c))
+    # the automatic choice (most of these batches go through materialised
+    # scores) and the fused tiling
+    for variant in (0, B.idb_router_variant_info(T, d, E, K, B.IDB_DTYPE_BF16, 0)["variant"]):
+        rs = RouterStep(T, d, E, K, torch.bfloat16, B.ControllerCfg(E, Ki, Kd, mode, center), variant=variant, device=DEV)
+        rs.step(xt, Wt)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(rs.idx.cpu().numpy(), r_idx)
+        np.testing.assert_array_equal(rs.counts.cpu().numpy(), r_c)
+        np.testing.assert_allclose(rs.w.cpu().numpy(), r_w, rtol=2e-5)
+        np.testing.assert_array_equal(rs.state.bias.cpu().numpy(), ref.bias)
+        np.testing.assert_array_equal(rs.state.e_prev.cpu().numpy(), ref.e_prev)
+        np.testing.assert_array_equal(rs.stats.cpu().numpy(), oracle.load_stats(r_c))
 
 
 def _qb_cases(n=24):
