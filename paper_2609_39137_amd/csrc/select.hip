@@ -426,14 +426,18 @@ __global__ __launch_bounds__(64 * WAVES) void select_reg_kernel(RouterArgs a, co
 
 // Workgroup shape.  Every workgroup flushes its histogram with one device
 // atomic per non-zero bin, so fewer, larger workgroups issue fewer atomics to
-// the same few counters; small batches leave CUs idle that way and take smaller
-// ones.  us for 4, 8 and 16 waves: E = 768, K = 10: T = 64 8.2, 8.3, 9.0; E = 256,
-// K = 4: T = 256 6.8, 6.8, 7.5, T = 2048 9.0, 8.4, 8.3, T = 4096 11.8, 10.1, 8.7; E =
-// 96, K = 4: T = 4096 12.3, 10.0, 8.7.  Larger K: more work per token and group
-// maximum; E = 256, K = 16: T = 4096 -, 11.7, 12.4; E = 32, K = 32: T = 8192 -, 12.4, 13.7.
+// the same few counters; small batches leave CUs idle that way and take 8 waves,
+// the longer the rows and the larger K (the more work per token) the longer.  us
+// for 4, 8 and 16 waves: E = 96, K = 4: T = 1536 8.4, 7.5, 7.6, T = 4096 12.2, 9.3, 8.4;
+// E = 256, K = 4: T = 2048 9.1, 7.9, 8.0, T = 4096 11.8, 9.3, 8.6; E = 512, K = 4: T = 4096
+// 11.5, 9.7, 9.5, K = 8 12.8, 10.4, 10.4; E = 1024, K = 4: T = 2560 10.4, 10.0, 11.7, T =
+// 4096 11.9, 11.0, 12.0; E = 256, K = 16: T = 4096 14.5, 11.7, 12.1; E = 32, K = 32: T =
+// 8192 -, 12.4, 13.7.  The smallest batches with several group maxima gain 1 to 5%
+// on 4 waves (E = 1024, K = 20: T = 64 13.6, 14.0, 14.0).
 constexpr int kRegWaves = 16;
-constexpr int kRegFewTokens = 256;        // up to here 4 waves
-constexpr int kRegTokensPerGroup = 2048;  // up to G times this 8 waves
+template <int NV, int G>
+constexpr int64_t kRegFewTokens = G > 1 ? 2048 * G : NV >= 8 ? 4096 : 2048;  // up to here 8 waves
+constexpr int64_t kRegTinyTokens = 256;  // G > 1: up to here 4
 
 template <int NV, int WAVES, int G>
 hipError_t launch_select_waves(const RouterArgs& a, const float* scores, const CtrlArgs& ctrl, int cus,
@@ -459,8 +463,10 @@ hipError_t launch_select_reg(const RouterArgs& a, const float* scores, const Ctr
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         cus = 256;
-    if (a.T <= kRegFewTokens) return launch_select_waves<NV, 4, G>(a, scores, ctrl, cus, stream);
-    if (a.T <= kRegTokensPerGroup * G) return launch_select_waves<NV, 8, G>(a, scores, ctrl, cus, stream);
+    if constexpr (G > 1) {
+        if (a.T <= kRegTinyTokens) return launch_select_waves<NV, 4, G>(a, scores, ctrl, cus, stream);
+    }
+    if (a.T <= kRegFewTokens<NV, G>) return launch_select_waves<NV, 8, G>(a, scores, ctrl, cus, stream);
     // the widest rows with several group maxima need more than the 128 VGPRs of
     // a 16-wave workgroup
     constexpr int waves = (NV >= 16 && G >= 2) || (NV >= 12 && G == 4) ? kRegWaves / 2 : kRegWaves;
