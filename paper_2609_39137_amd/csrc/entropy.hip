@@ -4,8 +4,8 @@
 //   H_full = -sum_e p_e log p_e, p_e = c_e / C, c_e = max(fl32(s_e + b_e), 0),
 //            C = sum_e c_e, evaluated as log C - ln 2 (sum_e c_e log2 c_e) / C
 //            (H_full = 0 when C = 0), each c_e log2 c_e with the hardware
-//            fp32 log2 and summed in fp64 (terms with c_e below the smallest
-//            normal fp32 count as 0).
+//            fp32 log2 and summed in fp64 (below the smallest normal fp32 c_e
+//            keeps its value and takes that number's logarithm).
 // The softmax form (the auxiliary-loss router, whose selection scores are the
 // softmax probabilities of its logits): H_full = log Z - (sum_e t_e (z_e - M))
 // / Z with M the token's largest logit, t_e = exp(z_e - M) from the hardware
@@ -22,10 +22,15 @@ namespace idb {
 
 namespace {
 
-constexpr int kEntThreads = 512;
-constexpr int kEntWaves = kEntThreads / 64;
 constexpr int kEntAhead = 2;  // rows a wave has in flight
+// Up to this many tokens a workgroup has 256 threads, else 512: fewer waves to
+// start and to reduce over when most have no token or one.  us, 256 / 512 threads:
+// softmax, K = 1: T = 200, E = 1024 6.8 / 7.7; T = 4096, E = 256 7.2 / 8.2; T = 8192, E =
+// 256 8.8 / 9.3; T = 16384, E = 512 13.6 / 13.3, E = 404 14.7 / 13.9; T = 65536, E = 768
+// 44.6 / 39.7.
+constexpr int64_t kEntFewTokens = 8192;
 
+template <int NT>
 __device__ inline double block_sum_fixed(double v, double* red) {
     // fixed butterfly inside each wave, then the waves in order
 #pragma unroll
@@ -34,7 +39,7 @@ __device__ inline double block_sum_fixed(double v, double* red) {
     if (lane == 0) red[wv] = v;
     __syncthreads();
     double t = 0.0;
-    for (int w = 0; w < kEntWaves; ++w) t += red[w];
+    for (int w = 0; w < NT / 64; ++w) t += red[w];
     __syncthreads();
     return t;
 }
@@ -131,14 +136,16 @@ __device__ inline double entropy_of(double C, double D) {
 // block's run of tokens.  At T = 16384, E = 768, K = 10: 14.4 us (3.5 TB/s;
 // 18.0 us with a logarithm and a division per token in every lane, one row
 // ahead and two shuffles per reduction step).
-template <bool SOFTMAX, int NP>
-__global__ __launch_bounds__(kEntThreads) void entropy_partial_kernel(const float* __restrict__ w, int64_t T, int K,
+template <bool SOFTMAX, int NP, int NT>
+__global__ __launch_bounds__(NT) void entropy_partial_kernel(const float* __restrict__ w, int64_t T, int K,
                                                                       const float* __restrict__ scores,
                                                                       const float* __restrict__ bias, int E,
                                                                       double* __restrict__ partial) {
-    __shared__ double red[kEntWaves];
+    constexpr int NW = NT / 64;
+    __shared__ double red[NW];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int64_t first = (int64_t)blockIdx.x * kEntWaves + wv, step = (int64_t)gridDim.x * kEntWaves;
+    const int64_t first = (int64_t)blockIdx.x * NW + wv;
+    constexpr int64_t step = (int64_t)kEntropyBlocks * NW;
     constexpr float kPad = SOFTMAX ? -INFINITY : 0.0f;
     float buf[kEntAhead][4 * NP], b[4 * NP];
     if (scores) {
@@ -148,9 +155,9 @@ __global__ __launch_bounds__(kEntThreads) void entropy_partial_kernel(const floa
         if constexpr (!SOFTMAX) load_row<NP>(bias, E, 0.0f, b);
     }
     // H_topK: terms of the block's tokens (0 log 0 = 0)
-    const int64_t t_lo = T * blockIdx.x / gridDim.x, t_hi = T * (blockIdx.x + 1) / gridDim.x;
+    const int64_t t_lo = T * blockIdx.x / kEntropyBlocks, t_hi = T * (blockIdx.x + 1) / kEntropyBlocks;
     double htop = 0.0;
-    for (int64_t i = t_lo * K + tid; i < t_hi * K; i += kEntThreads) {
+    for (int64_t i = t_lo * K + tid; i < t_hi * K; i += NT) {
         const double x = (double)w[i];
         if (x > 0.0) htop -= x * log(x);
     }
@@ -182,8 +189,8 @@ __global__ __launch_bounds__(kEntThreads) void entropy_partial_kernel(const floa
         }
         if (lane < held) hfull += entropy_of<SOFTMAX>(myC, myD);
     }
-    const double stop = block_sum_fixed(htop, red);
-    const double sfull = block_sum_fixed(hfull, red);
+    const double stop = block_sum_fixed<NT>(htop, red);
+    const double sfull = block_sum_fixed<NT>(hfull, red);
     if (tid == 0) {
         partial[2 * blockIdx.x] = stop;
         partial[2 * blockIdx.x + 1] = sfull;
@@ -215,8 +222,12 @@ __global__ __launch_bounds__(64) void entropy_final_kernel(const double* __restr
 template <bool SOFTMAX, int NP>
 void launch_partial(const float* gate_w, int64_t T, int K, const float* scores, const float* bias, int E,
                     double* partial, hipStream_t stream) {
-    hipLaunchKernelGGL((entropy_partial_kernel<SOFTMAX, NP>), dim3(kEntropyBlocks), dim3(kEntThreads), 0, stream,
-                       gate_w, T, K, scores, bias, E, partial);
+    if (T <= kEntFewTokens)
+        hipLaunchKernelGGL((entropy_partial_kernel<SOFTMAX, NP, 256>), dim3(kEntropyBlocks), dim3(256), 0, stream,
+                           gate_w, T, K, scores, bias, E, partial);
+    else
+        hipLaunchKernelGGL((entropy_partial_kernel<SOFTMAX, NP, 512>), dim3(kEntropyBlocks), dim3(512), 0, stream,
+                           gate_w, T, K, scores, bias, E, partial);
 }
 
 }  // namespace

@@ -128,7 +128,8 @@ def test_one_layer_equals_the_single_layer_update():
         assert torch.equal(one.e_prev[0].view(torch.int32), single.e_prev.view(torch.int32))
 
 
-@pytest.mark.parametrize("T,E,K", [(2048, 768, 10), (1000, 64, 4), (300, 512, 3), (4097, 1024, 32)])
+@pytest.mark.parametrize("T,E,K", [(2048, 768, 10), (1000, 64, 4), (300, 512, 3), (4097, 1024, 32), (8192, 300, 2),
+                                   (8193, 64, 5), (9001, 1000, 10)])
 def test_routing_entropy_matches_oracle(T, E, K):
     r = synth.rng(T, E, K)
     w = r.random((T, K)).astype(np.float32) + np.float32(1e-3)
@@ -189,7 +190,7 @@ def test_softmax_routing_entropy_matches_oracle(T, E, K, scale):
 # at 4-byte alignment, one token, more tokens than a wave holds sums for (64 of
 # the grid's 4096 waves)
 @pytest.mark.parametrize("T,E,K", [(1, 1, 1), (5, 3, 2), (4097, 255, 3), (700, 257, 5), (333, 513, 8), (129, 769, 10),
-                                   (64, 1023, 32), (262145 + 7, 6, 2)])
+                                   (64, 1023, 32), (8193, 255, 3), (8200, 770, 2), (262145 + 7, 6, 2)])
 def test_routing_entropies_at_every_row_length(T, E, K):
     r = synth.rng(T, E, K, 9)
     w = r.random((T, K)).astype(np.float32) + np.float32(1e-3)
