@@ -432,12 +432,14 @@ __global__ __launch_bounds__(64 * WAVES) void select_reg_kernel(RouterArgs a, co
 // E = 256, K = 4: T = 2048 9.1, 7.9, 8.0, T = 4096 11.8, 9.3, 8.6; E = 512, K = 4: T = 4096
 // 11.5, 9.7, 9.5, K = 8 12.8, 10.4, 10.4; E = 1024, K = 4: T = 2560 10.4, 10.0, 11.7, T =
 // 4096 11.9, 11.0, 12.0; E = 256, K = 16: T = 4096 14.5, 11.7, 12.1; E = 32, K = 32: T =
-// 8192 -, 12.4, 13.7.  The smallest batches with several group maxima gain 1 to 5%
-// on 4 waves (E = 1024, K = 20: T = 64 13.6, 14.0, 14.0).
+// 8192 -, 12.4, 13.7.  Batches of several 4-wave workgroups, but few, gain up to 5%
+// on those (E = 1024, K = 20: T = 64 13.6, 14.0, 14.0), unless the last workgroup's
+// controller update, which has more threads in a larger one, weighs more (router
+// step, K <= 10, T = 32: 8 waves 0.94 of the time of 4).
 constexpr int kRegWaves = 16;
 template <int NV, int G>
 constexpr int64_t kRegFewTokens = G > 1 ? 2048 * G : NV >= 8 ? 4096 : 2048;  // up to here 8 waves
-constexpr int64_t kRegTinyTokens = 256;  // G > 1: up to here 4
+constexpr int64_t kRegOneTokens = 16, kRegTinyTokens = 256;  // above and up to these 4 waves
 
 template <int NV, int WAVES, int G>
 hipError_t launch_select_waves(const RouterArgs& a, const float* scores, const CtrlArgs& ctrl, int cus,
@@ -463,9 +465,8 @@ hipError_t launch_select_reg(const RouterArgs& a, const float* scores, const Ctr
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         cus = 256;
-    if constexpr (G > 1) {
-        if (a.T <= kRegTinyTokens) return launch_select_waves<NV, 4, G>(a, scores, ctrl, cus, stream);
-    }
+    if (a.T > kRegOneTokens && a.T <= kRegTinyTokens && (G == 4 || !ctrl.ticket))
+        return launch_select_waves<NV, 4, G>(a, scores, ctrl, cus, stream);
     if (a.T <= kRegFewTokens<NV, G>) return launch_select_waves<NV, 8, G>(a, scores, ctrl, cus, stream);
     // the widest rows with several group maxima need more than the 128 VGPRs of
     // a 16-wave workgroup

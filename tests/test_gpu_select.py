@@ -96,7 +96,7 @@ def test_gate_weights_sum_to_one_and_ignore_bias():
 
 # the last batch of each workgroup size (4, 8 and 16 waves) and the first of the
 # next, for each number of group maxima
-@pytest.mark.parametrize("T,K", [(2048, 10), (2049, 10), (4096, 10), (4097, 10), (256, 16), (257, 11), (4096, 16), (4097, 11),
+@pytest.mark.parametrize("T,K", [(16, 10), (17, 10), (256, 9), (257, 9), (2048, 10), (2049, 10), (4096, 10), (4097, 10), (256, 16), (257, 11), (4096, 16), (4097, 11),
                                  (257, 17), (8192, 32), (8193, 17)])
 @pytest.mark.parametrize("E", [64, 100, 384, 768, 1000])
 def test_workgroup_sizes(T, E, K):
