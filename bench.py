@@ -46,6 +46,12 @@ def log(msg: str) -> None:
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
+def step_path(rs) -> str:
+    """What ``rs.step`` runs with the packed router matrix: ``rs.info`` (and the ``roofline`` kernel, timed through the
+    split calls) describe the fused tiling also where the step goes through materialised scores."""
+    return "scores in memory, then selection" if rs.uses_scores(packed=True) else "fused tiling"
+
+
 def load_traffic(workload: str, variant_id: int, family: str = "router"):
     """HBM bytes per launch of a counted kernel (router, merge, select) from the committed counter summary, or
     None if it is stale (kernel sources changed since) or absent."""
@@ -209,7 +215,7 @@ def main() -> int:
     log("inputs resident on the GPU")
 
     rs = RouterStep(wl.T, wl.d, wl.E, wl.K, tdtype, B.ControllerCfg(wl.E, 6e-3, 6e-3), variant=args.variant)
-    log(f"router tiling {rs.info}")
+    log(f"router tiling {rs.info}; the step's path: {step_path(rs)}")
     stream = torch.cuda.Stream()  # default priority
     torch.cuda.synchronize()
 
@@ -468,7 +474,7 @@ def main() -> int:
         "dtype": wl.dtype,
         "data": "synthetic",
         "config": {"workload": wl.name, "T": wl.T, "d": wl.d, "E": wl.E, "K": wl.K, "global_batch": wl.T,
-                   "parallelism": "single GPU", "variant": rs.info["variant"],
+                   "parallelism": "single GPU", "variant": rs.info["variant"], "path": step_path(rs),
                    "launch": "eager" if args.eager else "one hip-graph per block of steps", "input_buffers": nbuf,
                    "weight": "bf16 row-major, repacked every step" if wl.dtype == "bf16" else
                              "fp32 row-major, repacked every step"},
@@ -656,7 +662,8 @@ def loop_markdown(out: dict, argv) -> str:
              f"{out['steps']} steps", "", "Command:", "", "```", "python " + " ".join(argv), "```", "",
              "Each step: a fresh synthetic batch routed by idb_router_step with the controller's current bias "
              "(the fused router kernel, then the slice merge with the update and MaxVio/MinVio in its last "
-             "workgroup, or the controller step when one slice covers all experts). "
+             "workgroup, or the controller step when one slice covers all experts; where the step takes the scored "
+             "path, the score kernel, then the selection with the update and MaxVio/MinVio in its last workgroup). "
              "Diagnostics from idb_controller_update_layers on a copy of the pre-step state (its bias equals the "
              "step's bit for bit, checked every step).", "",
              f"| controller | K_i | K_d | mode | centre | MaxVio last {last} | MaxVio avg | MaxVio worst | "

@@ -73,3 +73,16 @@ def test_cpu_baseline_leg_times_the_oracle_on_a_bounded_sample():
     assert r["value"] > 0 and r["single_thread_value"] > 0
     assert r["cores"] >= 1
     assert "oracle steps" in r["sample"] and wl.name in r["sample"]
+
+
+def test_the_step_s_path_is_named():
+    # the closed-loop workload of 4096 fp32 tokens goes through materialised scores, the headline through its tiling
+    from paper_2609_39137_amd import binding as B
+    from paper_2609_39137_amd.pipeline import RouterStep
+
+    for wl, code, path in (("tiny-e64-k4", B.IDB_DTYPE_F32, "scores in memory"), ("top10-of-768", B.IDB_DTYPE_BF16, "fused")):
+        w = synth.WORKLOADS[wl]
+        rs = RouterStep.__new__(RouterStep)  # no device tensors
+        rs.T, rs.d, rs.E, rs.K, rs.dtype_code, rs._whole_variant = w.T, w.d, w.E, w.K, code, B.IDB_ROUTER_AUTO_SCORES
+        rs.workspace = type("Bytes", (), {"numel": lambda self: 1 << 30})()
+        assert bench.step_path(rs).startswith(path)
