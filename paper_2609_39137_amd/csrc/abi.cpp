@@ -154,10 +154,14 @@ bool use_scores(int64_t T, int32_t d, int32_t E, int32_t K, const idb::RouterTil
 }
 
 // From this many tokens on the scored path packs a row-major router matrix
-// into its workspace first (about 4 us; T = 777 E = 256: 12.9 us unpacked, 11.9
-// packed; T = 1024 E = 1024: 40 us unpacked, 29 packed).  Not fp32, whose MFMAs
-// take long enough to cover the loads (T = 4096, d = 256, E = 64: 7.4 us
-// unpacked, 8.4 packed).
+// into its workspace first.  Whole steps, packed first / row-major, us, K = 8: the
+// larger the matrix and the more token tiles read it, the more the pack gives (E
+// = 1024, d = 4096: T = 777 39.5 / 54.5, T = 2560 57.4 / 86.1; E = 256, d = 4096: T = 777
+// 24.2 / 21.1, T = 1280 25.7 / 31.4; E = 768, d = 1024: T = 1024 23.7 / 21.1, T = 2560 29.0 /
+// 32.6), and a small matrix pays for the launch alone (E = 256, d = 256: T = 1024
+// 14.7 / 13.0, T = 2560 17.8 / 17.8; E = 64, d = 256: T = 2560 13.5 / 11.7): one line for
+// all of them.  Not fp32, whose MFMAs take long enough to cover the loads (T =
+// 4096, d = 256, E = 64: score kernel 7.4 us unpacked, 8.4 packed).
 constexpr int64_t kPackTokens = 1024;
 
 bool packs_first(int64_t T, idb_dtype dtype) { return T >= kPackTokens && dtype == IDB_DTYPE_BF16; }

@@ -2,8 +2,9 @@
 // rapid-update; SIGN mode: Eq. pid-deepseek) and MaxVio/MinVio (Eq. vio).
 //
 // The single-layer controller holds one expert per thread of one workgroup
-// (E <= 1024), the batched kernel a workgroup of 256 threads per layer; both
-// run controller_block, so they are bit-reproducible and give the same bits.  fp32 steps are evaluated exactly as written: no FMA
+// (E <= 1024), the batched kernel a workgroup of four waves, or with many layers
+// of one, per layer; all run controller_block, so they are bit-reproducible and
+// give the same bits.  fp32 steps are evaluated exactly as written: no FMA
 // contraction in this file.
 #include "common.h"
 #include "controller_block.h"
