@@ -450,50 +450,63 @@ __global__ __launch_bounds__(WAVES * 64) void router16_kernel(RouterArgs a, int 
     select_epilogue<EC, SM>(a, NS, slice, tok0, smem, breg, store_pass);
 }
 
+// How many of N keys are above k.  All reads come before the first compare; the
+// scheduler would else pair them one by one.
+template <int N>
+__device__ __forceinline__ int count_above(const unsigned long long* list, unsigned long long k) {
+    unsigned long long q[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) q[i] = list[i];
+    __builtin_amdgcn_sched_barrier(0);
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) n += q[i] > k ? 1 : 0;
+    return n;
+}
+
+// How a merge counts the keys above a candidate's in another slice's
+// rank-ordered (descending) list of KL keys.  A binary search finds that number,
+// but its probes depend on each other and, with lists of 8 or 16 keys, meet in a
+// few LDS banks; a scan of a short list reads 8 or 4 keys at once.  Whole steps,
+// scan against search, us: KL = 8: E = 800 T = 8192 d = 64 61.3 / 73.0, fp32 E = 1024
+// T = 2560 d = 32 51.2 / 66.7; KL = 3 and 7, whose searches take 2 and 3 probes: E =
+// 896 T = 9000 45.2 / 43.0 and 63.1 / 61.4; KL = 10: search 1.01 to 1.03 times the
+// scan; KL = 16: 1.01 to 1.10; KL = 12 and 14: 0.96 and 0.89 on average over 4
+// slices; KL > 16: 0.99.  A kernel for each form: with several in one, each costs
+// the others 1 to 5% of a step in scheduling.  (Two slices are merged by two
+// pointers.)
+enum MergeForm { kMergePair, kMergeScan8, kMergeScan, kMergeSearch };
+inline MergeForm merge_form(int KL) {
+    if (KL == 8 || KL == 16) return kMergeScan8;
+    return KL >= 4 && KL <= 10 && KL != 7 ? kMergeScan : kMergeSearch;
+}
+
 // The rank of a candidate with key k: r, its rank in its own slice sl, plus the
-// keys above k in the other slices' rank-ordered (descending) lists of KL keys,
-// slice o's at list + o KL.  The lists come sorted out of the epilogue, so a
-// binary search finds that number, but its probes depend on each other and, with
-// lists of 8 or 16 keys, meet in a few LDS banks; a scan of a short list reads 8
-// keys at once.  Whole steps, scan against search, us: KL = 8: E = 800 T = 8192
-// d = 64 61.3 / 73.0, fp32 E = 1024 T = 2560 d = 32 51.2 / 66.7; KL = 10: search 1.01
-// to 1.03 times the scan; KL = 16: 1.01 to 1.10; KL = 12 and 14: 0.96 and 0.89 on
-// average over 4 slices; KL > 16: 0.99.  The form is chosen outside the loop
-// over the slices.
+// keys above k in the other slices' lists, slice o's at list + o KL.
+template <MergeForm FORM>
 __device__ __forceinline__ int merged_rank(const unsigned long long* list, int NS, int KL, int sl, int r,
                                            unsigned long long k) {
     int rank = r;
-    if (KL <= 10 || KL == 16) {  // uniform: the list length of the launch
-        for (int o = 0; o < NS; ++o) {
-            if (o == sl) continue;
-            const unsigned long long* lo = list + o * KL;
-            int j = 0;
-            for (; j + 8 <= KL; j += 8) {
-                unsigned long long q[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) q[i] = lo[j + i];
-                // all reads before the first compare, which the scheduler
-                // would else pair one by one
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) rank += q[i] > k ? 1 : 0;
-            }
-#pragma unroll 1
-            for (; j < KL; ++j) rank += lo[j] > k ? 1 : 0;
-        }
-        return rank;
-    }
     for (int o = 0; o < NS; ++o) {
         if (o == sl) continue;
         const unsigned long long* lo = list + o * KL;
-        int below = 0, n = KL;
-        while (n > 0) {
-            const int half = n >> 1;
-            const bool above = lo[below + half] > k;
-            below = above ? below + half + 1 : below;
-            n = above ? n - half - 1 : half;
+        if constexpr (FORM == kMergeScan8) {
+            for (int j = 0; j < KL; j += 8) rank += count_above<8>(lo + j, k);
+        } else if constexpr (FORM == kMergeScan) {
+            int j = KL > 8 ? 8 : 4;
+            rank += KL > 8 ? count_above<8>(lo, k) : count_above<4>(lo, k);
+#pragma unroll 1
+            for (; j < KL; ++j) rank += lo[j] > k ? 1 : 0;
+        } else {
+            int below = 0, n = KL;
+            while (n > 0) {
+                const int half = n >> 1;
+                const bool above = lo[below + half] > k;
+                below = above ? below + half + 1 : below;
+                n = above ? n - half - 1 : half;
+            }
+            rank += below;
         }
-        rank += below;
     }
     return rank;
 }
@@ -508,6 +521,7 @@ __device__ __forceinline__ int merged_rank(const unsigned long long* list, int N
 constexpr int kMergeThreads = 256;
 constexpr int kMergeBlocks = 512;
 
+template <MergeForm FORM>
 __global__ __launch_bounds__(kMergeThreads) void router_merge_kernel(RouterArgs a, int NS, CtrlArgs c) {
     __shared__ int hist[1024];
     __shared__ unsigned long long key[kMergeThreads];
@@ -538,7 +552,7 @@ __global__ __launch_bounds__(kMergeThreads) void router_merge_kernel(RouterArgs 
         __syncthreads();
         int rank = r;
         if (act) {
-            rank = merged_rank(key + tt * per_tok, NS, KL, sl, r, k);
+            rank = merged_rank<FORM>(key + tt * per_tok, NS, KL, sl, r, k);
             if (rank < K) {
                 sel[tt * K + rank] = s;
                 a.idx[tok * K + rank] = e;
@@ -576,6 +590,7 @@ __global__ __launch_bounds__(kMergeThreads) void router_merge_kernel(RouterArgs 
 constexpr int kTileThreads = 512;
 constexpr int kTileTokens = 128;
 
+template <MergeForm FORM>
 __global__ __launch_bounds__(kTileThreads) void router_merge_tile_kernel(RouterArgs a, int NS, CtrlArgs c) {
     __shared__ int hist[1024];
     __shared__ unsigned long long mk[kTileTokens * 64];
@@ -627,7 +642,7 @@ __global__ __launch_bounds__(kTileThreads) void router_merge_tile_kernel(RouterA
         }
         if (g + gridDim.x < ntiles) fetch(g + gridDim.x);
         __syncthreads();
-        if (NS == 2) {
+        if constexpr (FORM == kMergePair) {
             // Each slice's list is in rank order: a two-pointer merge per
             // token (the lists hold KL distinct keys each; key 0 marks an
             // exhausted list).  Each list's key after its head is read ahead,
@@ -664,7 +679,7 @@ __global__ __launch_bounds__(kTileThreads) void router_merge_tile_kernel(RouterA
                 const int t = c / NSK, pos = c - t * NSK;
                 const int sl = pos / KL, r = pos - sl * KL;
                 const unsigned long long k = mk[c];
-                const int rank = merged_rank(mk + t * NSK, NS, KL, sl, r, k);
+                const int rank = merged_rank<FORM>(mk + t * NSK, NS, KL, sl, r, k);
                 if (rank < K) {
                     msel[t * kMaxK + rank] = ms[c];
                     midx[t * kMaxK + rank] = (int)~(unsigned)k;
@@ -851,15 +866,29 @@ hipError_t launch_router_merge(const RouterTiling& t, const RouterArgs& a, const
             cus = 256;
         int64_t blocks = (a.T + kTileTokens - 1) / kTileTokens;
         if (blocks > cus) blocks = cus;
-        hipLaunchKernelGGL(router_merge_tile_kernel, dim3((unsigned)blocks), dim3(kTileThreads), 0, stream, a, NS,
-                           c);
-        return hipGetLastError();
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kTileThreads), 0, stream, a, NS, c);
+            return hipGetLastError();
+        };
+        if (NS == 2) return launch(router_merge_tile_kernel<kMergePair>);
+        switch (merge_form(KL)) {
+            case kMergeScan8: return launch(router_merge_tile_kernel<kMergeScan8>);
+            case kMergeScan: return launch(router_merge_tile_kernel<kMergeScan>);
+            default: return launch(router_merge_tile_kernel<kMergeSearch>);
+        }
     }
     const int tpg = kMergeThreads / (NS * KL);
     int64_t groups = (a.T + tpg - 1) / tpg;
     if (groups > kMergeBlocks) groups = kMergeBlocks;
-    hipLaunchKernelGGL(router_merge_kernel, dim3((unsigned)groups), dim3(kMergeThreads), 0, stream, a, NS, c);
-    return hipGetLastError();
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(kMergeThreads), 0, stream, a, NS, c);
+        return hipGetLastError();
+    };
+    switch (merge_form(KL)) {
+        case kMergeScan8: return launch(router_merge_kernel<kMergeScan8>);
+        case kMergeScan: return launch(router_merge_kernel<kMergeScan>);
+        default: return launch(router_merge_kernel<kMergeSearch>);
+    }
 }
 
 hipError_t launch_pack_weight(const void* W, void* P, int E, int64_t row_bytes, hipStream_t stream) {
