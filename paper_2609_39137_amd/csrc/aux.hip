@@ -15,6 +15,14 @@ constexpr int kAuxWaves = kAuxThreads / 64;
 constexpr int kAuxBatch = 16;  // tile rows a wave has in flight
 static_assert(kAuxMaxBlocks <= 16, "the last workgroup reduces the records inside one row of 16 lanes");
 
+// Adds sum and takes mx, mn over lanes R apart of the 16-lane row (all active).
+template <int R>
+__device__ __forceinline__ void row_fold(long long& sum, int& mx, int& mn) {
+    sum += __builtin_bit_cast(long long, row_rot<R>(__builtin_bit_cast(double, sum)));
+    mx = max(mx, row_rot<R>(mx));
+    mn = min(mn, row_rot<R>(mn));
+}
+
 // One workgroup per 64 experts, lane = expert.  Wave w adds the tiles w,
 // w + 16, ... in order (kAuxBatch rows in flight); wave 0 adds the wave sums
 // in order and reduces over its experts; the workgroup that finishes last
@@ -118,14 +126,19 @@ __global__ __launch_bounds__(kAuxThreads) void aux_stats_kernel(const float* __r
             mx = __hip_atomic_load(&partial[lane].max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             mn = __hip_atomic_load(&partial[lane].min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+        // scalar reads and row rotations: a shuffle is an LDS round trip, which
+        // cost more than one or two records' loads in turn (E <= 128)
+        const unsigned long long fb = __builtin_bit_cast(unsigned long long, fp);
         double L = 0.0;
-        for (int q = 0; q < nb; ++q) L = L + __shfl(fp, q);
-#pragma unroll
-        for (int o = 8; o >= 1; o >>= 1) {
-            sum += __shfl_xor(sum, o);
-            mx = max(mx, __shfl_xor(mx, o));
-            mn = min(mn, __shfl_xor(mn, o));
+        for (int q = 0; q < nb; ++q) {
+            const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)fb, q);
+            const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(fb >> 32), q);
+            L = L + __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
         }
+        row_fold<8>(sum, mx, mn);
+        row_fold<4>(sum, mx, mn);
+        row_fold<2>(sum, mx, mn);
+        row_fold<1>(sum, mx, mn);
         if (lane == 0) {
             *loss = alpha * L;
             if (stats) {
