@@ -107,9 +107,10 @@ size_t router_ws_bytes(int64_t T, int32_t E, int32_t K, const idb::RouterTiling&
 // of the fused tiling t.  It has small tiles for small batches and a selection
 // that keeps its speed for large K, but writes and reads T x E scores, so the
 // fused kernel takes over as the batch grows, and sooner the less contraction
-// there is to gain from (small d).  The lines lie where whole steps cross or,
-// where the lists of the fused epilogue make its time jump with the data, where
-// no measured shape lost to the fused kernels (scored / fused, us):
+// there is to gain from (small d).  The lines lie about where whole steps cross
+// (scored / fused, us).  For K = 13 and 14 that is no sharp line: one token whose
+// list overflows costs its fused tile about 10 us, so the fused time jumps with
+// the data (E = 768, K = 13, d = 64: T = 8192 33 / 34, T = 16384 42 / 32, T = 24000 50 / 58).
 //  - fp32: E = 256 T = 8192 45.5 / 53.9, T = 12288 60.5 / 54.5 (d = 2048); E = 128
 //    T = 16384 d = 256 33.7 / 36.8, d = 64 27.0 / 24.9; E = 64 T = 32768 d = 64 29.4 / 26.7
 //  - 128-expert tiles: E = 128 T = 16384 d = 2048 32.4 / 38.9, d = 64 21.9 / 21.2;
